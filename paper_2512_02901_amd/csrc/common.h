@@ -13,7 +13,7 @@ hipError_t launch_to_widely_linear(const float* A, int64_t N, int64_t K, float2*
                                    hipStream_t stream);
 
 // ------------------------------------------------------------- quantize ---
-// Workspace layout of the quantiser: one partial superaccumulator per block.
+// Workspace of the quantiser: 16 copies of each stage's exact totals.
 constexpr int kQzThreads = 256;
 constexpr int kQzMaxBlocks = 1024;
 size_t quantize_workspace_bytes(int64_t N, int64_t K);

@@ -38,65 +38,14 @@ FAIRY2I_HD inline void sa_split(double v, int* limb, uint32_t* lo, uint32_t* mid
   *hi = (uint32_t)(sh == 0 ? 0 : (M >> (64 - sh)));
 }
 
-// Loops over the words run with constant indices (fully unrolled on the
-// device), so the words stay in registers: every word a position selects is
-// picked by comparison, never by a computed index.
-#ifdef __HIP_DEVICE_COMPILE__
-#define SA_UNROLL _Pragma("unroll")
-#else
-#define SA_UNROLL
-#endif
-
-// Round (sum of limbs) * 2^-1074 / n to the nearest float32, ties to even.
-// `limbs` may be unnormalised (each < 2^63); n >= 1 and n <= 2^31.
-FAIRY2I_HD inline float sa_mean_to_f32(const uint64_t* limbs, uint64_t n) {
-  uint32_t w[SA_LIMBS + 1];
-  uint64_t carry = 0;
-  SA_UNROLL
-  for (int i = 0; i < SA_LIMBS; ++i) {
-    const uint64_t v = limbs[i] + carry;
-    w[i] = (uint32_t)v;
-    carry = v >> 32;
-  }
-  w[SA_LIMBS] = (uint32_t)carry;
-  int h = -1;  // highest nonzero word
-  SA_UNROLL
-  for (int i = 0; i <= SA_LIMBS; ++i)
-    if (w[i] != 0) h = i;
-  if (h < 0) return 0.0f;
-  uint32_t wh = 0;
-  SA_UNROLL
-  for (int i = 0; i <= SA_LIMBS; ++i)
-    if (i == h) wh = w[i];
-  const int bitlen = 32 * h + (32 - __builtin_clz(wh));
-  // S64 = top 64 bits of the sum (bit bitlen-1 becomes bit 63), sticky = any
-  // bit below them is set.
-  uint64_t S64;
-  bool sticky = false;
-  int shift = bitlen - 64;  // S = S64 * 2^shift + low bits
-  if (shift <= 0) {
-    uint64_t S = (uint64_t)w[0] | ((h >= 1 ? (uint64_t)w[1] : 0ull) << 32);
-    S64 = S << (-shift);
-  } else {
-    const int ws = shift >> 5, bs = shift & 31;
-    uint32_t a0 = 0, a1 = 0, a2 = 0;  // words ws, ws + 1, ws + 2 (0 past the top)
-    SA_UNROLL
-    for (int i = 0; i <= SA_LIMBS; ++i) {
-      if (i == ws) a0 = w[i];
-      if (i == ws + 1) a1 = w[i];
-      if (i == ws + 2) a2 = w[i];
-      if (i < ws && w[i] != 0) sticky = true;
-    }
-    const uint64_t lo64 = (uint64_t)a0 | ((uint64_t)a1 << 32);
-    const uint64_t top = (uint64_t)a2;
-    S64 = bs == 0 ? lo64 : ((lo64 >> bs) | (top << (64 - bs)));
-    if (bs != 0 && (a0 & ((1u << bs) - 1u)) != 0) sticky = true;
-  }
-  // value = (S64 + frac) * 2^shift * 2^-1074 / n = (q + delta) * 2^E
+// Round (S64 + f) * 2^E / n to the nearest float32, ties to even, where S64
+// has its top bit set, 0 <= f < 1 and `sticky` says whether f > 0; n >= 1 and
+// n <= 2^31.
+FAIRY2I_HD inline float sa_round_mean(uint64_t S64, bool sticky, int E, uint64_t n) {
+  // value = (q + delta) * 2^E
   const uint64_t q = S64 / n;
-  const uint64_t r = S64 % n;
+  const uint64_t r = S64 - q * n;
   if (r != 0) sticky = true;
-  const int E = shift - 1074;
   const int qb = 64 - __builtin_clzll(q);  // q >= 2^32 since S64 >= 2^63, n <= 2^31
   const int ebit = qb - 1 + E;             // value in [2^ebit, 2^(ebit+1))
   const bool subnormal = ebit < -126;
@@ -125,4 +74,47 @@ FAIRY2I_HD inline float sa_mean_to_f32(const uint64_t* limbs, uint64_t n) {
   __builtin_memcpy(&f, &out, 4);
 #endif
   return f;
+}
+
+// Round (sum of limbs) * 2^-1074 / n to the nearest float32, ties to even.
+// Only limbs lo .. hi may be nonzero and limb hi is (hi < 0: all are zero).
+// Limbs may be unnormalised (each < 2^63); n >= 1 and n <= 2^31.  The words
+// pass through a window of the four highest, so nothing is indexed but the
+// limbs themselves (LDS on the device).
+FAIRY2I_HD inline float sa_mean_range(const uint64_t* limbs, int lo, int hi, uint64_t n) {
+  if (hi < 0) return 0.0f;
+  uint64_t carry = 0;
+  uint32_t q3 = 0, q2 = 0, q1 = 0, q0 = 0;  // the words up to the current one, highest first
+  uint32_t below = 0;                       // or of all words under the window
+  for (int i = lo; i <= hi; ++i) {
+    const uint64_t v = limbs[i] + carry;
+    below |= q0;
+    q0 = q1;
+    q1 = q2;
+    q2 = q3;
+    q3 = (uint32_t)v;
+    carry = v >> 32;
+  }
+  int top = hi;  // index of the word in q3
+  if (carry) {
+    below |= q0;
+    q0 = q1;
+    q1 = q2;
+    q2 = q3;
+    q3 = (uint32_t)carry;
+    ++top;
+  }
+  // q3 != 0: limb hi (plus what it was carried) is not zero
+  const int z = __builtin_clz(q3);
+  const uint64_t h64 = ((uint64_t)q3 << 32) | q2, l64 = ((uint64_t)q1 << 32) | q0;
+  const uint64_t S64 = z ? (h64 << z) | (l64 >> (64 - z)) : h64;
+  const bool sticky = below != 0 || (l64 << z) != 0;
+  return sa_round_mean(S64, sticky, 32 * (top + 1) - z - 64 - 1074, n);
+}
+
+// sa_mean_range over all SA_LIMBS limbs.
+FAIRY2I_HD inline float sa_mean_to_f32(const uint64_t* limbs, uint64_t n) {
+  int hi = SA_LIMBS - 1;
+  while (hi >= 0 && limbs[hi] == 0) --hi;
+  return sa_mean_range(limbs, 0, hi, n);
 }

@@ -1,0 +1,79 @@
+"""Edges of the kernels' tilings and value ranges, against the CPU oracle."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from oracle import groups as og
+
+pytestmark = pytest.mark.gpu
+
+
+def dev(a, gpu):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a)).to(gpu)
+
+
+def host(t):
+    return t.detach().cpu().numpy()
+
+
+def wide_matrix(N, K, spread):
+    """Complex entries over 2^-spread .. 2^spread of 1, zeros and the smallest and largest floats among them."""
+    rng = np.random.default_rng((N, K, spread))
+    re, im = (rng.standard_normal((N, K)) * np.exp2(rng.uniform(-spread, spread, (N, K))) for _ in range(2))
+    M = (re + 1j * im).astype(np.complex64)
+    flat = M.reshape(-1)
+    for i, v in enumerate((0, complex(-0.0, 0.0), 2.0 ** -149, 2.0 ** -149 * 1j, 2.0 ** 120, 1 + 1j, -1 + 1j)):
+        if spread > 20:
+            flat[(37 * i + 11) % flat.size] = v
+    return M
+
+
+# ---------------------------------------------------- exact axis scales ---
+# spread 60: most values lie outside the fixed-point window of their wave and
+# take the limbs in LDS; leading zero rows: the window is placed late.
+
+@pytest.mark.parametrize("spread", [0, 20, 60])
+@pytest.mark.parametrize("N,K,T,zero_rows", [(5, 20, 4, 0), (33, 260, 2, 0), (64, 512, 3, 40)])
+def test_quantize_value_ranges(gpu, N, K, T, zero_rows, spread):
+    import paper_2512_02901_amd as f2
+    M = wide_matrix(N, K, spread)
+    M[:zero_rows] = 0
+    codes, scales = oracle.quantize(M, T)
+    c, s = f2.quantize(dev(M, gpu), T)
+    np.testing.assert_array_equal(host(s).view(np.uint32), scales.view(np.uint32))
+    np.testing.assert_array_equal(host(c), oracle.pack(codes))
+
+
+def test_quantize_many_values_a_lane(gpu):
+    """2^28 + 2^20 entries: a lane's sums pass through a flush.  All entries
+    have the same two magnitudes, so the scales are those exactly."""
+    import torch
+    import paper_2512_02901_amd as f2
+    N, K = 32896, 8192
+    M = torch.full((N, K), 0.7109375 - 0.01j, dtype=torch.complex64, device=gpu)
+    M[:, ::3] = 0.02 + 0.33j
+    codes, scales = f2.quantize(M, 1)
+    assert scales.tolist() == [[0.7109375, float(np.float32(0.33))]]
+    want = torch.zeros(K, dtype=torch.uint8, device=gpu)
+    want[::3] = 1
+    want = want.view(-1, 4) << torch.tensor([0, 2, 4, 6], dtype=torch.uint8, device=gpu)
+    assert bool((codes[0] == want.sum(1, dtype=torch.uint8)).all())
+
+
+# every lane count per group, one to four bytes a lane, the long-group kernel; ragged last groups
+@pytest.mark.parametrize("G,K", [(4, 20), (8, 52), (12, 100), (32, 100), (64, 260), (128, 300), (256, 776),
+                                 (512, 1156), (1020, 2044), (1024, 1028), (1028, 2200)])
+@pytest.mark.parametrize("spread,off", [(1, 0), (60, 1)])
+def test_quantize_grouped_edges(gpu, G, K, spread, off):
+    import torch
+    import paper_2512_02901_amd as f2
+    N, T = 7, 3
+    M = wide_matrix(N, K, spread)
+    codes, scales = og.quantize_grouped(M, T, G)
+    buf = torch.empty(N * K + off, dtype=torch.complex64, device=gpu)  # off = 1: 8 bytes off 16-byte alignment
+    buf[off:] = dev(M, gpu).reshape(-1)
+    c, s = f2.quantize_grouped(buf[off:].view(N, K), T, G)
+    np.testing.assert_array_equal(host(s).view(np.uint32), scales.view(np.uint32))
+    np.testing.assert_array_equal(host(c), oracle.pack(codes))
