@@ -504,7 +504,7 @@ fairy2i_status fairy2i_qat_fake_quant(const float* M, int64_t N, int64_t K, int3
  *   H += (s_re Re G_Q + b_re d_re) + i (s_im Im G_Q + b_im d_im),
  *   d_re = sum_j Re(G_Q_j) b_re_j / n_re,  d_im likewise (0 when empty).
  * The sums are taken in double in a fixed order (bitwise reproducible); H is
- * kept in g_master as complex64.  codes, scales: as written by
+ * carried in double and rounded once.  codes, scales: as written by
  * fairy2i_qat_fake_quant.  workspace: fairy2i_qat_ste_workspace_bytes(N, K).
  * Errors: FAIRY2I_ERR_NULL; FAIRY2I_ERR_SHAPE (as fairy2i_quantize);
  * FAIRY2I_ERR_STAGES; FAIRY2I_ERR_WORKSPACE.

@@ -6,8 +6,9 @@
 //                       in double and rounded once to float32 or bf16
 //   ste_*_kernel        straight-through backward through the stage
 //                       recursion (b(.) with an identity Jacobian, scales
-//                       differentiated through their masked means), stages
-//                       in reverse order, reductions in a fixed order
+//                       differentiated through their masked means): one pass
+//                       for all stages' sums in a fixed order, one for the
+//                       gradient
 //   cgemm_gauss_kernel  complex GEMM with Gauss's three real products,
 //                       P1 = Ar Br, P2 = Ai Bi, P3 = (Ar + Ai)(Br + Bi),
 //                       C = (P1 - P2) + i (P3 - P1 - P2), on the bf16 matrix
@@ -78,222 +79,258 @@ __global__ __launch_bounds__(kQatThreads) void fq_dequant_kernel(const uint8_t* 
 }
 
 // ----------------------------------------------------- STE backward ---
-// Stage t of the reverse recursion, with H = dL/dR_{t+1} held in g_master
-// (zero before the last stage) and G = dL/dW^:
-//   G_Q = G - H;  d_re = sum_j Re G_Q_j b_re_j / n_re,  d_im likewise;
-//   H  += (s_re Re G_Q + b_re d_re) + i (s_im Im G_Q + b_im d_im).
+// Stage t of the reverse recursion, with H = dL/dR_{t+1} (zero before the
+// last stage) and G = dL/dW^, on each axis of its own:
+//   G_Q = G - H;  d_t = sum_j G_Q_j b_t_j / n_t;  H += s_t G_Q + b_t d_t.
+// H is a combination of G and of the later stages' signs with scalar
+// coefficients, H = a G + sum_{u > t} c_u b_u, so every d_t follows from
+//   A_t = sum_j G_j b_t_j,  n_t,  and C_tu = sum_j b_t_j b_u_j (an integer):
+//   d_t = ((1 - a) A_t - sum_{u > t} c_u C_tu) / n_t.
+// One pass over G and the codes forms those sums for every stage; a second
+// runs the whole recursion per entry in double and writes H once.  (A pass
+// per stage that wrote H and read it back, 62 us per 2048 x 2048 matrix at
+// T = 2, moved 200 MB; these two move 102 MB in 32 us.)
+//
+// Both passes take chunks of 4 code bytes a thread (16 entries), byte u of a
+// thread kThreads bytes after byte u - 1, so that a wave's loads are
+// contiguous runs of 32 bytes a lane.
 
-struct StePart {
-  double sum[2];
-  unsigned long long n[2];
+constexpr int kSteThreads = 512;     // reducing pass
+constexpr int kSteMaxBlocks = 512;   // its blocks, each with one SteSums in the workspace
+
+struct SteSums {
+  double a[FAIRY2I_MAX_STAGES][2];  // A_t on the real and the imaginary axis
+  int32_t odd[FAIRY2I_MAX_STAGES];  // entries of stage t on the imaginary axis
+  int32_t c[FAIRY2I_MAX_STAGES * (FAIRY2I_MAX_STAGES - 1) / 2][2];  // C_tu, pair (t, u) at u (u - 1) / 2 + t, t < u
 };
 
-__device__ inline double block_sum_double(double v, double* sh) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  const int w = threadIdx.x >> 6;
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) sh[w] = v;
-  __syncthreads();
-  double s = 0.0;
-  for (int i = 0; i < (int)(blockDim.x >> 6); ++i) s += sh[i];  // fixed order
-  return s;
-}
-
-__device__ inline unsigned long long block_sum_u64(unsigned long long v, unsigned long long* sh) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  const int w = threadIdx.x >> 6;
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) sh[w] = v;
-  __syncthreads();
-  unsigned long long s = 0;
-  for (int i = 0; i < (int)(blockDim.x >> 6); ++i) s += sh[i];
-  return s;
-}
-
-// Each thread takes units of 16 entries: 4 code bytes (entry e is code
-// (byte[e / 4] >> 2 (e % 4)) & 3) and 128 bytes of G and of H, as 16-byte
-// loads when G and H are 16-byte aligned (VEC) and the unit is whole; a last,
-// partial unit goes one entry at a time.  FIRST: the first stage of the
-// reverse recursion, where H is still zero (not read, only written).
-template <bool VEC>
-__device__ inline int ste_unit(const uint8_t* __restrict__ codes_t, const float2* __restrict__ p, int64_t u,
-                               int64_t nelem, uint32_t& c, float2 (&v)[16]) {
-  const int64_t e0 = 16 * u;
-  const int n = nelem - e0 < 16 ? (int)(nelem - e0) : 16;
-  c = 0u;
-  for (int b = 0; b < (n + 3) / 4; ++b) c |= (uint32_t)codes_t[4 * u + b] << (8 * b);
-  if (VEC && n == 16) {
-    const float4* q = reinterpret_cast<const float4*>(p + e0);
+template <typename V>
+__device__ inline V wave_add(V v) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const float4 f = q[i];
-      v[2 * i] = make_float2(f.x, f.y);
-      v[2 * i + 1] = make_float2(f.z, f.w);
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  return v;
+}
+
+// The codes of every stage (byte u of the thread at bits 8 u) and, with
+// ENTRIES, the 16 entries of G of one chunk.  Returns how many of the four
+// bytes exist.  VEC: G is 16-byte aligned.
+template <int T, bool VEC>
+__device__ inline int ste_chunk(const uint8_t* __restrict__ codes, const float2* __restrict__ G, int64_t b0,
+                                int64_t step, int64_t nbytes, uint32_t (&c)[T], float2 (&g)[16]) {
+  int n = 0;
+#pragma unroll
+  for (int t = 0; t < T; ++t) c[t] = 0u;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int64_t bi = b0 + u * step;
+    if (bi < nbytes) {
+      ++n;
+#pragma unroll
+      for (int t = 0; t < T; ++t) c[t] |= (uint32_t)codes[(int64_t)t * nbytes + bi] << (8 * u);
+      if constexpr (VEC) {
+        const float4* q = reinterpret_cast<const float4*>(G + 4 * bi);
+        const float4 f0 = q[0], f1 = q[1];
+        g[4 * u] = make_float2(f0.x, f0.y);
+        g[4 * u + 1] = make_float2(f0.z, f0.w);
+        g[4 * u + 2] = make_float2(f1.x, f1.y);
+        g[4 * u + 3] = make_float2(f1.z, f1.w);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) g[4 * u + e] = G[4 * bi + e];
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) g[4 * u + e] = make_float2(0.0f, 0.0f);
     }
-  } else {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) v[i] = i < n ? p[e0 + i] : make_float2(0.0f, 0.0f);
   }
   return n;
 }
 
-template <bool VEC>
-__device__ inline void ste_h16(const float2* __restrict__ p, int64_t u, int n, float2 (&v)[16]) {
-  const int64_t e0 = 16 * u;
-  if (VEC && n == 16) {
-    const float4* q = reinterpret_cast<const float4*>(p + e0);
+template <int T, bool VEC>
+__global__ __launch_bounds__(kSteThreads) void ste_sums_kernel(const uint8_t* __restrict__ codes,
+                                                               const float2* __restrict__ G, int64_t nbytes,
+                                                               SteSums* __restrict__ part) {
+  constexpr int NP = T * (T - 1) / 2, W = kSteThreads / 64;
+  __shared__ double sha[W][T][2];
+  __shared__ int32_t shi[W][T + 2 * NP + 1];
+  double a[T][2];
+  int32_t odd[T], cc[NP + 1][2];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const float4 f = q[i];
-      v[2 * i] = make_float2(f.x, f.y);
-      v[2 * i + 1] = make_float2(f.z, f.w);
+  for (int t = 0; t < T; ++t) a[t][0] = a[t][1] = 0.0, odd[t] = 0;
+#pragma unroll
+  for (int p = 0; p < NP; ++p) cc[p][0] = cc[p][1] = 0;
+  for (int64_t k0 = (int64_t)blockIdx.x * 4 * kSteThreads; k0 < nbytes; k0 += (int64_t)gridDim.x * 4 * kSteThreads) {
+    uint32_t c[T];
+    float2 g[16];
+    const int n = ste_chunk<T, VEC>(codes, G, k0 + threadIdx.x, kSteThreads, nbytes, c, g);
+    const uint32_t valid = n == 4 ? 0x55555555u : 0x55555555u & ((1u << (8 * n)) - 1u);
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const uint32_t k = c[t] >> (2 * e);
+        const bool im = k & 1u;
+        // the chosen component with its sign; the other axis adds +-0
+        const uint32_t sg = (k & 2u) << 30;
+        a[t][0] += (double)(im ? 0.0f : __uint_as_float(__float_as_uint(g[e].x) ^ sg));
+        a[t][1] += (double)(im ? __uint_as_float(__float_as_uint(g[e].y) ^ sg) : 0.0f);
+      }
+      odd[t] += __builtin_popcount(c[t] & valid);
     }
-  } else {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) v[i] = i < n ? p[e0 + i] : make_float2(0.0f, 0.0f);
+    for (int u = 1; u < T; ++u)
+#pragma unroll
+      for (int t = 0; t < u; ++t) {
+        const uint32_t both1 = c[t] & c[u] & valid, both0 = ~(c[t] | c[u]) & valid, diff = (c[t] ^ c[u]) >> 1;
+        cc[u * (u - 1) / 2 + t][0] += __builtin_popcount(both0) - 2 * __builtin_popcount(both0 & diff);
+        cc[u * (u - 1) / 2 + t][1] += __builtin_popcount(both1) - 2 * __builtin_popcount(both1 & diff);
+      }
+  }
+  // fixed-order sums: the wave's butterfly, then the waves in order
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    const double s0 = wave_add(a[t][0]), s1 = wave_add(a[t][1]);
+    const int32_t o = wave_add(odd[t]);
+    if (lane == 0) sha[wave][t][0] = s0, sha[wave][t][1] = s1, shi[wave][t] = o;
+  }
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    const int32_t x = wave_add(cc[p][0]), y = wave_add(cc[p][1]);
+    if (lane == 0) shi[wave][T + 2 * p] = x, shi[wave][T + 2 * p + 1] = y;
+  }
+  __syncthreads();
+  SteSums& out = part[blockIdx.x];
+  if (threadIdx.x < 2 * T) {
+    double s = 0.0;
+    for (int w = 0; w < W; ++w) s += sha[w][threadIdx.x >> 1][threadIdx.x & 1];
+    out.a[threadIdx.x >> 1][threadIdx.x & 1] = s;
+  } else if (threadIdx.x >= 64 && threadIdx.x < 64 + T + 2 * NP) {
+    const int i = threadIdx.x - 64;
+    int32_t s = 0;
+    for (int w = 0; w < W; ++w) s += shi[w][i];
+    if (i < T) out.odd[i] = s;
+    else out.c[(i - T) >> 1][(i - T) & 1] = s;
   }
 }
 
-template <bool VEC, bool FIRST>
-__global__ __launch_bounds__(kQatThreads) void ste_reduce_kernel(const uint8_t* __restrict__ codes_t,
-                                                                 const float2* __restrict__ G,
-                                                                 const float2* __restrict__ H, int64_t nelem,
-                                                                 StePart* __restrict__ part) {
-  __shared__ double shd[kQatThreads / 64];
-  __shared__ unsigned long long shn[kQatThreads / 64];
-  double s_re = 0.0, s_im = 0.0;
-  unsigned long long n_re = 0, n_im = 0;
-  const int64_t nunits = (nelem + 15) / 16;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < nunits; u += stride) {
-    uint32_t c;
-    float2 g[16], h[16];
-    const int n = ste_unit<VEC>(codes_t, G, u, nelem, c, g);
-    if constexpr (!FIRST) ste_h16<VEC>(H, u, n, h);
-    // every entry predicated, no early exit: a fully unrolled loop with
-    // constant indices keeps g and h in registers
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const uint32_t k = (c >> (2 * e)) & 3u;
-      const double gq_re = FIRST ? (double)g[e].x : (double)g[e].x - (double)h[e].x;
-      const double gq_im = FIRST ? (double)g[e].y : (double)g[e].y - (double)h[e].y;
-      const double sg = (k & 2u) ? -1.0 : 1.0;  // codes 2, 3 are -1, -i
-      // selects, not a branch on which sum to bump (that also puts the pair
-      // in scratch memory)
-      const bool on = e < n, odd = (k & 1u) != 0u;
-      s_im = (on && odd) ? s_im + sg * gq_im : s_im;
-      s_re = (on && !odd) ? s_re + sg * gq_re : s_re;
-      n_im += (on && odd) ? 1ull : 0ull;
-      n_re += (on && !odd) ? 1ull : 0ull;
-    }
-  }
-  const double a = block_sum_double(s_re, shd);
-  const double b = block_sum_double(s_im, shd);
-  const unsigned long long na = block_sum_u64(n_re, shn);
-  const unsigned long long nb = block_sum_u64(n_im, shn);
-  if (threadIdx.x == 0) {
-    part[blockIdx.x].sum[0] = a;
-    part[blockIdx.x].sum[1] = b;
-    part[blockIdx.x].n[0] = na;
-    part[blockIdx.x].n[1] = nb;
-  }
-}
-
-// NEXT: the update also forms the next (lower) stage's reduction from the H
-// it has just written (codes_n: that stage's codes), with the same threads,
-// units and order as ste_reduce_kernel, into part_n: one pass over G and H
-// instead of two per stage.
-template <bool VEC, bool FIRST, bool NEXT>
-__global__ __launch_bounds__(kQatThreads) void ste_update_kernel(const uint8_t* __restrict__ codes_t,
-                                                                 const float* __restrict__ scales_t,
-                                                                 const float2* __restrict__ G,
-                                                                 float2* __restrict__ H, int64_t nelem,
-                                                                 const StePart* __restrict__ part, int nblk,
-                                                                 const uint8_t* __restrict__ codes_n,
-                                                                 StePart* __restrict__ part_n) {
-  // d[axis] = (sum of the reduction blocks' partial sums) / n, formed by every
-  // block alike: thread i sums partials i, i + 256, ... in order, then the
-  // block's fixed-order tree, so every block (and every run) gets the same d
-  __shared__ double shd[kQatThreads / 64];
-  __shared__ unsigned long long shn[kQatThreads / 64];
-  double a = 0.0, b = 0.0;
-  unsigned long long na = 0, nb = 0;
-  for (int i = threadIdx.x; i < nblk; i += blockDim.x) {
-    a += part[i].sum[0];
-    b += part[i].sum[1];
-    na += part[i].n[0];
-    nb += part[i].n[1];
-  }
-  a = block_sum_double(a, shd);
-  b = block_sum_double(b, shd);
-  na = block_sum_u64(na, shn);
-  nb = block_sum_u64(nb, shn);
-  const double s_re = (double)scales_t[0], s_im = (double)scales_t[1];
-  const double d_re = na ? a / (double)na : 0.0, d_im = nb ? b / (double)nb : 0.0;
-  double x_re = 0.0, x_im = 0.0;  // the next stage's sums
-  unsigned long long xn_re = 0, xn_im = 0;
-  const int64_t nunits = (nelem + 15) / 16;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < nunits; u += stride) {
-    uint32_t c, cn = 0u;
-    float2 g[16], h[16];
-    const int n = ste_unit<VEC>(codes_t, G, u, nelem, c, g);
-    if constexpr (NEXT)
-      for (int bb = 0; bb < (n + 3) / 4; ++bb) cn |= (uint32_t)codes_n[4 * u + bb] << (8 * bb);
-    if constexpr (FIRST) {
-#pragma unroll
-      for (int e = 0; e < 16; ++e) h[e] = make_float2(0.0f, 0.0f);
+template <int T, bool VEC>
+__global__ __launch_bounds__(kQatThreads) void ste_apply_kernel(const uint8_t* __restrict__ codes,
+                                                                const float* __restrict__ scales,
+                                                                const float2* __restrict__ G, int64_t nbytes,
+                                                                const SteSums* __restrict__ part, int nblk,
+                                                                float2* __restrict__ H) {
+  // the sums' totals and the d_t, formed by every block alike: each wave adds
+  // a share of the totals over all partials (64 at a time, then the wave's
+  // butterfly), so every block (and every run) gets the same d
+  constexpr int NP = T * (T - 1) / 2;
+  __shared__ double sha[T][2];
+  __shared__ int64_t shi[T + 2 * NP + 1];
+  __shared__ double shd[T][2];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int v = wave; v < 2 * T + T + 2 * NP; v += kQatThreads / 64) {
+    if (v < 2 * T) {
+      double s = 0.0;
+      for (int i = lane; i < nblk; i += 64) s += part[i].a[v >> 1][v & 1];
+      s = wave_add(s);
+      if (lane == 0) sha[v >> 1][v & 1] = s;
     } else {
-      ste_h16<VEC>(H, u, n, h);
+      const int w = v - 2 * T;
+      long long s = 0;
+      for (int i = lane; i < nblk; i += 64) s += w < T ? part[i].odd[w] : part[i].c[(w - T) >> 1][(w - T) & 1];
+      s = wave_add(s);
+      if (lane == 0) shi[w] = s;
     }
-    float2 o[16];
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    const int ax = threadIdx.x;
+    double coef = 0.0, later[T];  // H = coef G + sum later[u] b_u
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const uint32_t k = (c >> (2 * e)) & 3u;
-      const double gq_re = (double)g[e].x - (double)h[e].x, gq_im = (double)g[e].y - (double)h[e].y;
-      const double sg = (k & 2u) ? -1.0 : 1.0;
-      const double b_re = (k & 1u) ? 0.0 : sg;
-      const double b_im = (k & 1u) ? sg : 0.0;
-      const double nr = (double)h[e].x + (s_re * gq_re + b_re * d_re);
-      const double ni = (double)h[e].y + (s_im * gq_im + b_im * d_im);
-      o[e] = make_float2((float)nr, (float)ni);
-      if constexpr (NEXT) {
-        // the next stage's G_Q from the stored (float32) H, as its own reduction would read it
-        if (e < n) {
-          const uint32_t kn = (cn >> (2 * e)) & 3u;
-          const double sn = (kn & 2u) ? -1.0 : 1.0;
-          if (kn & 1u) {
-            x_im += sn * ((double)g[e].y - (double)o[e].y);
-            ++xn_im;
-          } else {
-            x_re += sn * ((double)g[e].x - (double)o[e].x);
-            ++xn_re;
-          }
+    for (int t = T - 1; t >= 0; --t) {
+      const int64_t n = ax ? shi[t] : 4 * nbytes - shi[t];
+      double q = (1.0 - coef) * sha[t][ax];
+#pragma unroll
+      for (int u = t + 1; u < T; ++u) q -= later[u] * (double)shi[T + 2 * (u * (u - 1) / 2 + t) + ax];
+      const double d = n ? q / (double)n : 0.0;
+      const double s = (double)scales[2 * t + ax];
+      coef += s * (1.0 - coef);
+#pragma unroll
+      for (int u = t + 1; u < T; ++u) later[u] *= 1.0 - s;
+      later[t] = d;
+      shd[t][ax] = d;
+    }
+  }
+  __syncthreads();
+  double s_re[T], s_im[T], d_re[T], d_im[T];
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    s_re[t] = (double)scales[2 * t];
+    s_im[t] = (double)scales[2 * t + 1];
+    d_re[t] = shd[t][0];
+    d_im[t] = shd[t][1];
+  }
+  for (int64_t k0 = (int64_t)blockIdx.x * 4 * kQatThreads; k0 < nbytes; k0 += (int64_t)gridDim.x * 4 * kQatThreads) {
+    uint32_t c[T];
+    float2 g[16];
+    const int64_t b0 = k0 + threadIdx.x;
+    const int n = ste_chunk<T, VEC>(codes, G, b0, kQatThreads, nbytes, c, g);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      float2 o[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const double gr = (double)g[4 * u + e].x, gi = (double)g[4 * u + e].y;
+        double hr = 0.0, hi = 0.0;
+#pragma unroll
+        for (int t = T - 1; t >= 0; --t) {
+          const uint32_t k = c[t] >> (8 * u + 2 * e);
+          const double sg = (k & 2u) ? -1.0 : 1.0;
+          const double b_re = (k & 1u) ? 0.0 : sg, b_im = (k & 1u) ? sg : 0.0;
+          hr += s_re[t] * (gr - hr) + b_re * d_re[t];
+          hi += s_im[t] * (gi - hi) + b_im * d_im[t];
+        }
+        o[e] = make_float2((float)hr, (float)hi);
+      }
+      if (u < n) {
+        float2* dst = H + 4 * (b0 + (int64_t)u * kQatThreads);
+        if constexpr (VEC) {
+          reinterpret_cast<float4*>(dst)[0] = make_float4(o[0].x, o[0].y, o[1].x, o[1].y);
+          reinterpret_cast<float4*>(dst)[1] = make_float4(o[2].x, o[2].y, o[3].x, o[3].y);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dst[e] = o[e];
         }
       }
     }
-    if (VEC && n == 16) {
-      float4* q = reinterpret_cast<float4*>(H + 16 * u);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) q[i] = make_float4(o[2 * i].x, o[2 * i].y, o[2 * i + 1].x, o[2 * i + 1].y);
-    } else {
-#pragma unroll
-      for (int e = 0; e < 16; ++e)
-        if (e < n) H[16 * u + e] = o[e];  // constant indices: o stays in registers
-    }
   }
-  if constexpr (NEXT) {
-    const double xa = block_sum_double(x_re, shd);
-    const double xb = block_sum_double(x_im, shd);
-    const unsigned long long xna = block_sum_u64(xn_re, shn);
-    const unsigned long long xnb = block_sum_u64(xn_im, shn);
-    if (threadIdx.x == 0) {
-      part_n[blockIdx.x].sum[0] = xa;
-      part_n[blockIdx.x].sum[1] = xb;
-      part_n[blockIdx.x].n[0] = xna;
-      part_n[blockIdx.x].n[1] = xnb;
-    }
-  }
+}
+
+int ste_blocks(int64_t nbytes) {
+  const int64_t b = (nbytes + 4 * kSteThreads - 1) / (4 * kSteThreads);
+  return (int)(b > kSteMaxBlocks ? kSteMaxBlocks : b);
+}
+
+template <int T, bool VEC>
+hipError_t launch_ste(const uint8_t* codes, const float* scales, const float2* G, float2* H, int64_t nbytes,
+                      SteSums* part, hipStream_t s) {
+  const int nblk = ste_blocks(nbytes);
+  hipLaunchKernelGGL((ste_sums_kernel<T, VEC>), dim3(nblk), dim3(kSteThreads), 0, s, codes, G, nbytes, part);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  int64_t blocks = (nbytes + 4 * kQatThreads - 1) / (4 * kQatThreads);
+  if (blocks > kQatMaxBlocks) blocks = kQatMaxBlocks;
+  hipLaunchKernelGGL((ste_apply_kernel<T, VEC>), dim3((unsigned)blocks), dim3(kQatThreads), 0, s, codes, scales, G,
+                     nbytes, part, nblk, H);
+  return hipGetLastError();
+}
+
+template <int T>
+hipError_t launch_ste_t(const uint8_t* codes, const float* scales, const float2* G, float2* H, int64_t nbytes,
+                        SteSums* part, hipStream_t s) {
+  const bool vec = ((reinterpret_cast<uintptr_t>(G) | reinterpret_cast<uintptr_t>(H)) & 15) == 0;
+  return vec ? launch_ste<T, true>(codes, scales, G, H, nbytes, part, s)
+             : launch_ste<T, false>(codes, scales, G, H, nbytes, part, s);
 }
 
 int qat_blocks(int64_t nbytes) {
@@ -516,7 +553,7 @@ fairy2i_status fairy2i_qat_fake_quant(const float* M, int64_t N, int64_t K, int3
 
 size_t fairy2i_qat_ste_workspace_bytes(int64_t N, int64_t K) {
   if (N <= 0 || K <= 0 || (K % 4) != 0) return 0;
-  return 2 * (size_t)qat_blocks((N * K + 15) / 16) * sizeof(StePart);  // this stage's partials and the next's
+  return (size_t)ste_blocks(N * K / 4) * sizeof(SteSums);
 }
 
 fairy2i_status fairy2i_qat_ste_backward(const uint8_t* codes, const float* scales, int32_t T, int64_t N, int64_t K,
@@ -526,44 +563,9 @@ fairy2i_status fairy2i_qat_ste_backward(const uint8_t* codes, const float* scale
   if (N <= 0 || K <= 0 || (K % 4) != 0 || N > FAIRY2I_MAX_QUANTIZE_ENTRIES / K) return FAIRY2I_ERR_SHAPE;
   if (T < 1 || T > FAIRY2I_MAX_STAGES) return FAIRY2I_ERR_STAGES;
   if (!workspace || workspace_bytes < fairy2i_qat_ste_workspace_bytes(N, K)) return FAIRY2I_ERR_WORKSPACE;
-  const hipStream_t s = qat_stream(stream);
-  const int64_t nelem = N * K, nbytes = nelem / 4;
-  const int nblk = qat_blocks((nelem + 15) / 16);
-  auto* part = static_cast<StePart*>(workspace);
-  const auto* G = reinterpret_cast<const float2*>(g_hat);
-  auto* H = reinterpret_cast<float2*>(g_master);
-  const bool vec = ((reinterpret_cast<uintptr_t>(g_hat) | reinterpret_cast<uintptr_t>(g_master)) & 15) == 0;
-  hipError_t e = hipSuccess;
-  // the last stage's reduction reads G only (H is still zero); every update
-  // but the first stage's also forms the next stage's reduction
-  StePart* cur = part;
-  StePart* nxt = part + nblk;
-  {
-    const uint8_t* ct = codes + (int64_t)(T - 1) * nbytes;
-    if (vec) hipLaunchKernelGGL((ste_reduce_kernel<true, true>), dim3(nblk), dim3(kQatThreads), 0, s, ct, G, H, nelem, cur);
-    else hipLaunchKernelGGL((ste_reduce_kernel<false, true>), dim3(nblk), dim3(kQatThreads), 0, s, ct, G, H, nelem, cur);
-    e = hipGetLastError();
-  }
-  for (int t = T - 1; t >= 0 && e == hipSuccess; --t) {
-    const uint8_t* ct = codes + (int64_t)t * nbytes;
-    const uint8_t* cn = t > 0 ? codes + (int64_t)(t - 1) * nbytes : nullptr;
-    const bool first = t == T - 1;  // H is still zero: not read, only written
-    const bool next = t > 0;
-    using K = void (*)(const uint8_t*, const float*, const float2*, float2*, int64_t, const StePart*, int,
-                       const uint8_t*, StePart*);
-    const K kernels[2][2][2] = {
-        {{ste_update_kernel<false, false, false>, ste_update_kernel<false, false, true>},
-         {ste_update_kernel<false, true, false>, ste_update_kernel<false, true, true>}},
-        {{ste_update_kernel<true, false, false>, ste_update_kernel<true, false, true>},
-         {ste_update_kernel<true, true, false>, ste_update_kernel<true, true, true>}}};
-    hipLaunchKernelGGL(kernels[vec][first][next], dim3(nblk), dim3(kQatThreads), 0, s, ct, scales + 2 * t, G, H,
-                       nelem, cur, nblk, cn, nxt);
-    e = hipGetLastError();
-    StePart* tmp = cur;
-    cur = nxt;
-    nxt = tmp;
-  }
-  return qat_status(e);
+  auto* launch = T == 1 ? launch_ste_t<1> : T == 2 ? launch_ste_t<2> : T == 3 ? launch_ste_t<3> : launch_ste_t<4>;
+  return qat_status(launch(codes, scales, reinterpret_cast<const float2*>(g_hat), reinterpret_cast<float2*>(g_master),
+                           N * K / 4, static_cast<SteSums*>(workspace), qat_stream(stream)));
 }
 
 fairy2i_status fairy2i_cgemm_gauss(const fairy2i_cgemm_operand* A, const fairy2i_cgemm_operand* B, const int64_t* K,

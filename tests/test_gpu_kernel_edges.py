@@ -5,6 +5,7 @@ import pytest
 import oracle
 import synth
 from oracle import groups as og
+from oracle import qat as oq
 
 pytestmark = pytest.mark.gpu
 
@@ -77,3 +78,21 @@ def test_quantize_grouped_edges(gpu, G, K, spread, off):
     c, s = f2.quantize_grouped(buf[off:].view(N, K), T, G)
     np.testing.assert_array_equal(host(s).view(np.uint32), scales.view(np.uint32))
     np.testing.assert_array_equal(host(c), oracle.pack(codes))
+
+
+# ------------------------------------------------- training-step kernels ---
+# nbytes = N K / 4 around a chunk of the two straight-through passes (2048 and
+# 1024 code bytes), and one with more chunks than blocks would take at once
+
+@pytest.mark.parametrize("N,K,T", [(1, 4, 1), (1, 4, 4), (3, 1364, 3), (1, 4096, 2), (1, 4100, 4), (2, 8192, 2),
+                                   (5, 8196, 3), (2100, 2048, 2)])
+def test_ste_backward_edges(gpu, N, K, T):
+    import paper_2512_02901_amd as f2
+    rng = np.random.default_rng(N + K + T)
+    codes = rng.integers(0, 4, (T, N, K))
+    scales = (0.3 * np.exp2(-np.arange(T))[:, None] * rng.uniform(0.9, 1.1, (T, 2))).astype(np.float32)
+    G = (rng.standard_normal((N, K)) + 1j * rng.standard_normal((N, K))).astype(np.complex64)
+    want = oq.ste_backward(codes, scales, G.astype(np.complex128))
+    got = host(f2.qat_ste_backward(dev(oracle.pack(codes), gpu), dev(scales, gpu), dev(G, gpu)))
+    # double sums and recursion, one rounding to float32
+    assert np.linalg.norm(got - want) <= 1e-7 * np.linalg.norm(want)
