@@ -86,14 +86,92 @@ __global__ __launch_bounds__(256) void unrealify_grad_kernel(const float2* __res
   }
 }
 
-// R straight from the codes (Eq. ifairy-dequant, Eq. res-sum): one thread
-// per packed byte, i.e. four entries (n, 4 j .. 4 j + 3) of U and of W, each
-// summed over the stages in increasing order in double (as the fake-quant
-// dequantisation does), their block entries formed in double and rounded
-// once to bf16; a 16-byte store per row of the block pair.  A stage adds
-// s c with c in {1, 0, -1} as one fused multiply-add: the same rounding as
-// adding or subtracting s, or nothing (a sum never holds -0, and the scales
-// are not negative), without a branch on the code.
+// The block entries of one (n, k) from the codes of its stages (Eq.
+// ifairy-dequant, Eq. res-sum): U^ and W^ are summed over the stages in
+// increasing order in double (as the fake-quant dequantisation does), the
+// entries formed in double and rounded once to bf16.  A stage adds s c with
+// c in {1, 0, -1} as one fused multiply-add: the same rounding as adding or
+// subtracting s, or nothing (a sum never holds -0, and the scales are not
+// negative), without a branch on the code.
+struct RealSum {
+  double ur, ui, wr, wi;
+};
+
+__device__ inline void real_add(RealSum& a, int ku, int kw, double sur, double sui, double swr, double swi) {
+  // i^k: 0 -> +1, 1 -> +i, 2 -> -1, 3 -> -i: real part 1 - k for even k, imaginary part 2 - k for odd k
+  const int cur = (1 - ku) & ((ku & 1) - 1), cui = (2 - ku) & -(ku & 1);
+  const int cwr = (1 - kw) & ((kw & 1) - 1), cwi = (2 - kw) & -(kw & 1);
+  a.ur = fma(sur, (double)cur, a.ur);
+  a.ui = fma(sui, (double)cui, a.ui);
+  a.wr = fma(swr, (double)cwr, a.wr);
+  a.wi = fma(swi, (double)cwi, a.wi);
+}
+
+// {row 2n, row 2n + 1} of the block, two bf16 entries each
+__device__ inline uint2 real_block(const RealSum& a) {
+  return make_uint2((uint32_t)bf16_from_double(a.ur + a.wr) | ((uint32_t)bf16_from_double(a.wi - a.ui) << 16),
+                    (uint32_t)bf16_from_double(a.ui + a.wi) | ((uint32_t)bf16_from_double(a.ur - a.wr) << 16));
+}
+
+// R straight from the codes for T <= 2: a (n, k) has 2T codes, so at most 256
+// different blocks exist.  Each thread block forms them all once in LDS (one
+// a thread, by the sums above) and then only looks them up: a code byte of
+// every plane in, two 16-byte stores out per four entries.  (Summing in
+// double for every entry was bound by that arithmetic: 2048 x 2048, T = 2,
+// 18.3 us, with the table 8.6 us for its 38 MB.)
+template <int T>
+__global__ __launch_bounds__(256) void realify_table_kernel(const uint8_t* __restrict__ cu,
+                                                            const float* __restrict__ su,
+                                                            const uint8_t* __restrict__ cw,
+                                                            const float* __restrict__ sw, int64_t N, int64_t K,
+                                                            uint4* __restrict__ R) {
+  static_assert(T == 1 || T == 2, "2T codes index at most 256 blocks");
+  __shared__ uint2 table[256];  // index: code of U's stage t at bits 2t, of W's at bits 4 + 2t
+  {
+    const int i = threadIdx.x;
+    RealSum a{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+      real_add(a, (i >> (2 * t)) & 3, (i >> (4 + 2 * t)) & 3, (double)su[2 * t], (double)su[2 * t + 1],
+               (double)sw[2 * t], (double)sw[2 * t + 1]);
+    table[i] = real_block(a);
+  }
+  __syncthreads();
+  const int64_t nbytes = N * K / 4, kb = K / 4, stride = (int64_t)gridDim.x * blockDim.x;
+  constexpr int U = 4;  // bytes a thread loads before it looks them up
+  for (int64_t b0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b0 < nbytes; b0 += U * stride) {
+    uint32_t u[U][T], w[U][T];
+#pragma unroll
+    for (int i = 0; i < U; ++i)
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        const int64_t bi = b0 + i * stride;
+        u[i][t] = bi < nbytes ? cu[(int64_t)t * nbytes + bi] : 0u;
+        w[i][t] = bi < nbytes ? cw[(int64_t)t * nbytes + bi] : 0u;
+      }
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      const int64_t bi = b0 + i * stride;
+      if (bi >= nbytes) break;
+      uint2 v[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        uint32_t idx = 0;
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+          idx |= (((u[i][t] >> (2 * e)) & 3u) << (2 * t)) | (((w[i][t] >> (2 * e)) & 3u) << (4 + 2 * t));
+        v[e] = table[idx];
+      }
+      const int64_t n = (int64_t)((uint32_t)bi / (uint32_t)kb), j = bi - n * kb;  // N K / 4 <= 2^28
+      R[(2 * n) * kb + j] = make_uint4(v[0].x, v[1].x, v[2].x, v[3].x);  // row 2n: K words, K / 4 uint4
+      R[(2 * n + 1) * kb + j] = make_uint4(v[0].y, v[1].y, v[2].y, v[3].y);
+    }
+  }
+}
+
+// The same for T >= 3, whose tables (4096 blocks and more) cost more to form
+// than the entries they would serve: every entry summed on its own.  One
+// thread per packed byte, i.e. four entries (n, 4 j .. 4 j + 3).
 __global__ __launch_bounds__(256) void realify_codes_kernel(const uint8_t* __restrict__ cu,
                                                             const float* __restrict__ su,
                                                             const uint8_t* __restrict__ cw,
@@ -102,8 +180,7 @@ __global__ __launch_bounds__(256) void realify_codes_kernel(const uint8_t* __res
   const int64_t nbytes = N * K / 4, kb = K / 4;
   for (int64_t bi = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; bi < nbytes;
        bi += (int64_t)gridDim.x * blockDim.x) {
-    double ur[4] = {0.0, 0.0, 0.0, 0.0}, ui[4] = {0.0, 0.0, 0.0, 0.0};
-    double wr[4] = {0.0, 0.0, 0.0, 0.0}, wi[4] = {0.0, 0.0, 0.0, 0.0};
+    RealSum a[4] = {};
 #pragma unroll
     for (int t = 0; t < FAIRY2I_MAX_STAGES; ++t) {
       if (t >= T) break;
@@ -111,33 +188,31 @@ __global__ __launch_bounds__(256) void realify_codes_kernel(const uint8_t* __res
       const double sur = (double)su[2 * t], sui = (double)su[2 * t + 1];
       const double swr = (double)sw[2 * t], swi = (double)sw[2 * t + 1];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int ku = (int)((bu >> (2 * e)) & 3u), kw = (int)((bw >> (2 * e)) & 3u);
-        // i^k: 0 -> +1, 1 -> +i, 2 -> -1, 3 -> -i: real part 1 - k for even k, imaginary part 2 - k for odd k
-        const int cur = (1 - ku) & ((ku & 1) - 1), cui = (2 - ku) & -(ku & 1);
-        const int cwr = (1 - kw) & ((kw & 1) - 1), cwi = (2 - kw) & -(kw & 1);
-        ur[e] = fma(sur, (double)cur, ur[e]);
-        ui[e] = fma(sui, (double)cui, ui[e]);
-        wr[e] = fma(swr, (double)cwr, wr[e]);
-        wi[e] = fma(swi, (double)cwi, wi[e]);
-      }
+      for (int e = 0; e < 4; ++e)
+        real_add(a[e], (int)((bu >> (2 * e)) & 3u), (int)((bw >> (2 * e)) & 3u), sur, sui, swr, swi);
     }
-    uint32_t top[4], bot[4];
+    uint2 v[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      top[e] = (uint32_t)bf16_from_double(ur[e] + wr[e]) | ((uint32_t)bf16_from_double(wi[e] - ui[e]) << 16);
-      bot[e] = (uint32_t)bf16_from_double(ui[e] + wi[e]) | ((uint32_t)bf16_from_double(ur[e] - wr[e]) << 16);
-    }
+    for (int e = 0; e < 4; ++e) v[e] = real_block(a[e]);
     const int64_t n = (int64_t)((uint32_t)bi / (uint32_t)kb), j = bi - n * kb;  // N K / 4 <= 2^28
-    R[(2 * n) * kb + j] = make_uint4(top[0], top[1], top[2], top[3]);  // row 2n: K words, K / 4 uint4
-    R[(2 * n + 1) * kb + j] = make_uint4(bot[0], bot[1], bot[2], bot[3]);
+    R[(2 * n) * kb + j] = make_uint4(v[0].x, v[1].x, v[2].x, v[3].x);
+    R[(2 * n + 1) * kb + j] = make_uint4(v[0].y, v[1].y, v[2].y, v[3].y);
   }
 }
 
-__global__ __launch_bounds__(256) void f32_to_bf16_kernel(const float* __restrict__ in, int64_t n,
+// Eight values a thread, as two 16-byte loads and one 16-byte store, where
+// both pointers are 16-byte aligned (`groups` of eight; the rest, and
+// everything otherwise, one at a time).  One value a thread moved the 100 MB
+// of 16.8 M values in 26 us (37 us from cold caches); this does in 15 (19).
+__global__ __launch_bounds__(256) void f32_to_bf16_kernel(const float* __restrict__ in, int64_t n, int64_t groups,
                                                           uint16_t* __restrict__ out) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    out[i] = bf16_rne_bits(in[i]);
+  const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = t0; i < groups; i += stride) {
+    const float4 a = reinterpret_cast<const float4*>(in)[2 * i], b = reinterpret_cast<const float4*>(in)[2 * i + 1];
+    auto pair = [](float x, float y) { return (uint32_t)bf16_rne_bits(x) | ((uint32_t)bf16_rne_bits(y) << 16); };
+    reinterpret_cast<uint4*>(out)[i] = make_uint4(pair(a.x, a.y), pair(a.z, a.w), pair(b.x, b.y), pair(b.z, b.w));
+  }
+  for (int64_t i = 8 * groups + t0; i < n; i += stride) out[i] = bf16_rne_bits(in[i]);
 }
 
 inline unsigned grid_for(int64_t n) {
@@ -171,8 +246,17 @@ fairy2i_status fairy2i_wl_realify_codes(const uint8_t* codes_U, const float* sca
   if (T < 1 || T > FAIRY2I_MAX_STAGES) return FAIRY2I_ERR_STAGES;
   if (N <= 0 || K <= 0 || K % 4 != 0 || N > ((int64_t)1 << 30) / K) return FAIRY2I_ERR_SHAPE;
   if (reinterpret_cast<uintptr_t>(R) & 15) return FAIRY2I_ERR_SHAPE;
-  hipLaunchKernelGGL(realify_codes_kernel, dim3(grid_for(N * K / 4)), dim3(256), 0, static_cast<hipStream_t>(stream),
-                     codes_U, scales_U, codes_W, scales_W, T, N, K, static_cast<uint4*>(R));
+  const hipStream_t st = static_cast<hipStream_t>(stream);
+  auto* out = static_cast<uint4*>(R);
+  if (T <= 2) {
+    // four bytes a thread, so a block's table serves 4096 entries
+    auto* kernel = T == 1 ? realify_table_kernel<1> : realify_table_kernel<2>;
+    hipLaunchKernelGGL(kernel, dim3(grid_for((N * K / 4 + 3) / 4)), dim3(256), 0, st, codes_U, scales_U, codes_W,
+                       scales_W, N, K, out);
+  } else {
+    hipLaunchKernelGGL(realify_codes_kernel, dim3(grid_for(N * K / 4)), dim3(256), 0, st, codes_U, scales_U, codes_W,
+                       scales_W, T, N, K, out);
+  }
   return hipGetLastError() == hipSuccess ? FAIRY2I_OK : FAIRY2I_ERR_HIP;
 }
 
@@ -189,8 +273,10 @@ fairy2i_status fairy2i_wl_unrealify_grad(const float* G_R, int64_t N, int64_t K,
 fairy2i_status fairy2i_f32_to_bf16(const float* in, int64_t n, void* out, void* stream) {
   if (!in || !out) return FAIRY2I_ERR_NULL;
   if (n <= 0) return FAIRY2I_ERR_SHAPE;
-  hipLaunchKernelGGL(f32_to_bf16_kernel, dim3(grid_for(n)), dim3(256), 0, static_cast<hipStream_t>(stream), in, n,
-                     static_cast<uint16_t*>(out));
+  const bool vec = ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 15) == 0;
+  const int64_t groups = vec ? n / 8 : 0;
+  hipLaunchKernelGGL(f32_to_bf16_kernel, dim3(grid_for(vec ? (n + 7) / 8 : n)), dim3(256), 0,
+                     static_cast<hipStream_t>(stream), in, n, groups, static_cast<uint16_t*>(out));
   return hipGetLastError() == hipSuccess ? FAIRY2I_OK : FAIRY2I_ERR_HIP;
 }
 

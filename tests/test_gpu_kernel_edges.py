@@ -96,3 +96,33 @@ def test_ste_backward_edges(gpu, N, K, T):
     got = host(f2.qat_ste_backward(dev(oracle.pack(codes), gpu), dev(scales, gpu), dev(G, gpu)))
     # double sums and recursion, one rounding to float32
     assert np.linalg.norm(got - want) <= 1e-7 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("n,off", [(1, 0), (7, 0), (8, 0), (9, 0), (4099, 0), (4096, 1), (1 << 20, 0)])
+def test_f32_to_bf16_edges(gpu, n, off):
+    import torch
+    import paper_2512_02901_amd as f2
+    rng = np.random.default_rng(n)
+    x = torch.from_numpy(rng.standard_normal(n + off).astype(np.float32))
+    x[off] = float("inf")
+    got = f2.f32_to_bf16(x.to(gpu)[off:])
+    assert torch.equal(got.cpu().view(torch.int16), x[off:].to(torch.bfloat16).view(torch.int16))
+
+
+@pytest.mark.parametrize("N,K,T", [(1, 4, 1), (3, 20, 2), (5, 1364, 1), (40, 2048, 2), (3, 20, 3)])
+def test_realify_codes_edges(gpu, N, K, T):
+    """R from the codes equals R from the float64 sums rounded once (bf16 of
+    the exact sum: the sums of a few float32 scales are exact in double)."""
+    import torch
+    import paper_2512_02901_amd as f2
+    rng = np.random.default_rng(N + K + T)
+    cu, cw = rng.integers(0, 4, (2, T, N, K))
+    su, sw = (0.02 * np.exp2(-np.arange(T))[None, :, None] * rng.uniform(0.9, 1.1, (2, T, 2))).astype(np.float32)
+    U, W = oracle.dequantize(cu, su), oracle.dequantize(cw, sw)
+    want = np.empty((N, 2, K, 2))
+    want[:, 0, :, 0], want[:, 0, :, 1] = U.real + W.real, W.imag - U.imag
+    want[:, 1, :, 0], want[:, 1, :, 1] = U.imag + W.imag, U.real - W.real
+    R = f2.wl_realify_codes(*(dev(a, gpu) for a in (oracle.pack(cu), su, oracle.pack(cw), sw)))
+    got = R.float().cpu().numpy().reshape(N, 2, K, 2).astype(np.float64)
+    assert np.all(np.abs(got - want) <= np.abs(want) * 2.0 ** -8)  # half a bf16 step
+    assert torch.isfinite(R).all()
