@@ -67,24 +67,22 @@ size_t single_decode_bytes(int64_t N, int64_t K, int32_t T, int64_t B, int32_t d
   return best;
 }
 
-fairy2i_status run_single_decode(DecLayer l, int32_t T, int32_t dtype, int64_t B, void* ws,
-                                 size_t ws_bytes, int32_t* acc, hipStream_t stream) {
-  DecHeader h = dec_header(T, dec_mode(dtype), B, acc != nullptr);
-  const size_t need = dec_layer_setup(l, h, true, nullptr);
-  if (!ws || ws_bytes < need) return FAIRY2I_ERR_WORKSPACE;
-  dec_layer_setup(l, h, true, static_cast<char*>(ws));
-  l.acc = acc;
-  l.item0 = 0;
-  l.step0 = 0;
-  h.n_layers = 1;
-  h.total_items = (int64_t)l.nrb * l.nkc;
-  h.total_steps = (int64_t)l.nrb * l.nk4;
-  h.max_nk4 = l.nk4;
-  const int64_t acc_elems = acc ? (int64_t)2 * T * 2 * B * l.N * 2 : 0;
-  return hip_status(launch_decode(h, l, nullptr, l.nkc > 1, B * (int64_t)l.N, acc != nullptr, acc_elems,
-                                  acc, stream));
-}
+// The split kernel's time grows with its blocks (16 rows x 16 tokens each),
+// the prefill GEMM's hardly at all while its own (32 x 64) do not fill the
+// GPU: they cross near this many.  T = 2, split / prefill, us: 2048 x 5504,
+// 128 tokens (1024 blocks) 31 / 46, 256 (2048) 58 / 50; 2048 x 2048, 128
+// tokens 15.8 / 20.9, 256 28.5 / 22.7; 5504 x 2048, 64 tokens (1376) 21 / 28,
+// 128 (2752) 37 / 30.
+constexpr int64_t kSplitBlocks = 1408;
 
+// The product of one layer (arguments and workspace checked).
+hipError_t launch_product(const WlArgs& a, void* workspace, hipStream_t s) {
+  const bool small = a.B <= FAIRY2I_MAX_DECODE_BATCH;
+  if (use_mfma_decode(a.dtype, a.N, a.K, small ? a.B : 1) &&
+      (small || (a.N + 15) / 16 * ((a.B + 15) / 16) <= kSplitBlocks))
+    return launch_split(a, s);
+  return small ? launch_gemv(a, s) : launch_gemm_i8(a, workspace, s);
+}
 
 // ------------------------------------------------ allocation-free call ---
 // fairy2i_wl_matmul_noalloc runs fairy2i_wl_matmul with this array as its
@@ -228,9 +226,6 @@ fairy2i_status fairy2i_wl_matmul(const uint8_t* codes_U, const float* scales_U,
   if (workspace_bytes < fairy2i_wl_matmul_workspace_bytes(N, K, T, B, dtype) ||
       (fairy2i_wl_matmul_workspace_bytes(N, K, T, B, dtype) > 0 && !workspace))
     return FAIRY2I_ERR_WORKSPACE;
-  if (use_mfma_decode(dtype, N, K, B))
-    return run_single_decode(dec_layer(codes_U, scales_U, codes_W, scales_W, N, K, x, x_scale, y), T,
-                             dtype, B, workspace, workspace_bytes, nullptr, as_stream(stream));
   WlArgs a{};
   a.codes[0] = codes_U;
   a.codes[1] = codes_W;
@@ -245,9 +240,7 @@ fairy2i_status fairy2i_wl_matmul(const uint8_t* codes_U, const float* scales_U,
   a.dtype = dtype;
   a.y = reinterpret_cast<float2*>(y);
   a.acc = nullptr;
-  const hipError_t e = (B <= FAIRY2I_MAX_DECODE_BATCH) ? launch_gemv(a, as_stream(stream))
-                                                       : launch_gemm_i8(a, workspace, as_stream(stream));
-  return hip_status(e);
+  return hip_status(launch_product(a, workspace, as_stream(stream)));
 }
 
 fairy2i_status fairy2i_wl_matmul_noalloc(const uint8_t* codes_U, const float* scales_U,
@@ -277,9 +270,6 @@ fairy2i_status fairy2i_wl_int8_accumulators(const uint8_t* codes_U, const uint8_
   if (workspace_bytes < fairy2i_wl_matmul_workspace_bytes(N, K, T, B, FAIRY2I_ACT_I8) ||
       (fairy2i_wl_matmul_workspace_bytes(N, K, T, B, FAIRY2I_ACT_I8) > 0 && !workspace))
     return FAIRY2I_ERR_WORKSPACE;
-  if (use_mfma_decode(FAIRY2I_ACT_I8, N, K, B))
-    return run_single_decode(dec_layer(codes_U, nullptr, codes_W, nullptr, N, K, q, nullptr, nullptr), T,
-                             FAIRY2I_ACT_I8, B, workspace, workspace_bytes, acc, as_stream(stream));
   WlArgs a{};
   a.codes[0] = codes_U;
   a.codes[1] = codes_W;
@@ -290,9 +280,7 @@ fairy2i_status fairy2i_wl_int8_accumulators(const uint8_t* codes_U, const uint8_
   a.x = q;
   a.dtype = FAIRY2I_ACT_I8;
   a.acc = acc;
-  const hipError_t e = (B <= FAIRY2I_MAX_DECODE_BATCH) ? launch_gemv(a, as_stream(stream))
-                                                       : launch_gemm_i8(a, workspace, as_stream(stream));
-  return hip_status(e);
+  return hip_status(launch_product(a, workspace, as_stream(stream)));
 }
 
 

@@ -126,3 +126,76 @@ def test_realify_codes_edges(gpu, N, K, T):
     got = R.float().cpu().numpy().reshape(N, 2, K, 2).astype(np.float64)
     assert np.all(np.abs(got - want) <= np.abs(want) * 2.0 ** -8)  # half a bf16 step
     assert torch.isfinite(R).all()
+
+
+# ------------------------------------------- one-launch products of a layer ---
+# rows and tokens around the 16 x 16 block, K around the 256-code steps and
+# the 64-code groups, fewer steps than waves and more; every T
+
+def layer(N, K, T, gpu, seed=0):
+    rng = np.random.default_rng((N, K, T, seed))
+    cu, cw = rng.integers(0, 4, (2, T, N, K))
+    su, sw = (0.02 * np.exp2(-np.arange(T))[None, :, None] * rng.uniform(0.9, 1.1, (2, T, 2))).astype(np.float32)
+    return (cu, su, cw, sw), tuple(dev(a, gpu) for a in (oracle.pack(cu), su, oracle.pack(cw), sw)), rng
+
+
+def offset_copy(t, off):
+    """The same values `off` elements past an aligned address."""
+    import torch
+    buf = torch.empty(t.numel() + off, dtype=t.dtype, device=t.device)
+    buf[off:] = t.reshape(-1)
+    return buf[off:].view(t.shape)
+
+
+SPLIT_SIZES = [(1, 64, 1), (15, 192, 2), (16, 256, 3), (17, 320, 16), (33, 2112, 17), (40, 5504, 33), (16, 1024, 47)]
+
+
+@pytest.mark.parametrize("T", [1, 2, 3, 4])
+@pytest.mark.parametrize("N,K,B", SPLIT_SIZES)
+def test_int8_layer_edges(gpu, N, K, B, T):
+    import paper_2512_02901_amd as f2
+    (cu, su, cw, sw), d, rng = layer(N, K, T, gpu)
+    q = rng.integers(-127, 128, (B, K, 2)).astype(np.int8)
+    f = rng.uniform(0.001, 0.02, B).astype(np.float32)
+    P = oracle.int8_accumulators(cu, cw, q)
+    for off in (0, 2):  # 2 bytes off: byte loads
+        dq = offset_copy(dev(q, gpu), off)
+        np.testing.assert_array_equal(host(f2.int8_accumulators(d[0], d[2], dq)), P)
+        y = host(f2.wl_matmul(*d, dq, dev(f, gpu)))
+        want = oracle.combine_accumulators(P, su, sw, f)
+        # exact integers, double sums, one rounding
+        assert np.linalg.norm(y - want) <= 1e-7 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("T", [1, 2, 3, 4])
+@pytest.mark.parametrize("N,K,B", [(n, k, min(b, 16)) for n, k, b in SPLIT_SIZES])
+def test_bf16_layer_edges(gpu, N, K, B, T):
+    import torch
+    import paper_2512_02901_amd as f2
+    (cu, su, cw, sw), d, rng = layer(N, K, T, gpu)
+    x = synth.bf16_round_complex(rng.standard_normal((B, K)) + 1j * rng.standard_normal((B, K)))
+    x[B // 2] *= 0  # a token of zeros
+    xd = dev(np.stack([x.real, x.imag], -1).astype(np.float32), gpu).to(torch.bfloat16)
+    want = oracle.wl_matmul(cu, su, cw, sw, x)
+    for off in (0, 1):
+        y = host(f2.wl_matmul(*d, offset_copy(xd, off)))
+        # values within 2^14 of the largest are exact in 23 bits, the rest off by 2^-23 of it at most
+        assert np.linalg.norm(y - want) <= 3e-7 * np.linalg.norm(want)
+        assert not y[B // 2].any()
+
+
+@pytest.mark.parametrize("B,K,off", [(1, 4, 0), (3, 2048, 0), (2, 8192, 0), (2, 8196, 0), (5, 1500, 1), (2, 6, 0)])
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_act_quant_edges(gpu, B, K, off, dt):
+    """Around the eight-value groups and the most that a thread block keeps in
+    registers; misaligned tokens and odd widths go one value at a time."""
+    import torch
+    import paper_2512_02901_amd as f2
+    rng = np.random.default_rng(K)
+    x = synth.bf16_round_complex(rng.standard_normal((B, K)) + 1j * rng.standard_normal((B, K)))
+    x[B - 1, 1:] = 0
+    q, f = oracle.quantize_act_int8(x)
+    xd = dev(x, gpu) if dt == "f32" else dev(np.stack([x.real, x.imag], -1).astype(np.float32), gpu).to(torch.bfloat16)
+    gq, gf = f2.quantize_act_int8(offset_copy(xd, off))
+    np.testing.assert_array_equal(host(gq), q)
+    np.testing.assert_array_equal(host(gf), f)
