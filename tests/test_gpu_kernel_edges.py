@@ -199,3 +199,48 @@ def test_act_quant_edges(gpu, B, K, off, dt):
     gq, gf = f2.quantize_act_int8(offset_copy(xd, off))
     np.testing.assert_array_equal(host(gq), q)
     np.testing.assert_array_equal(host(gf), f)
+
+
+# --------------------------------------- float activations, vector units ---
+# rows around the four of a block, every token group, K around the 1024 codes
+# that a block's lanes take at once
+
+@pytest.mark.parametrize("T", [1, 2, 3, 4])
+@pytest.mark.parametrize("N,K,B", [(1, 4, 1), (3, 20, 2), (4, 1024, 3), (5, 1028, 4), (9, 1500, 5), (2, 2100, 7), (6, 100, 16)])
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_float_layer_edges(gpu, N, K, B, T, dt):
+    import torch
+    import paper_2512_02901_amd as f2
+    if dt == "bf16" and K % 64 == 0:
+        pytest.skip("the matrix cores take it")
+    (cu, su, cw, sw), d, rng = layer(N, K, T, gpu)
+    x = (rng.standard_normal((B, K)) + 1j * rng.standard_normal((B, K))).astype(np.complex64)
+    if dt == "bf16":
+        x = synth.bf16_round_complex(x)
+    xd = dev(x, gpu) if dt == "f32" else dev(np.stack([x.real, x.imag], -1).astype(np.float32), gpu).to(torch.bfloat16)
+    want = oracle.wl_matmul(cu, su, cw, sw, x)
+    # float32 sums of up to 4 K / 256 products a lane, then a tree: each term
+    # rounded at most 4 K / 256 + 10 times, against the 2-norm of the terms
+    R = np.abs(oracle.dequantize(cu, su)) + np.abs(oracle.dequantize(cw, sw))
+    bound = 2.0 ** -24 * (K / 64 + 14) * np.linalg.norm(np.abs(x) @ R.T)
+    for off in (0, 1):
+        y = host(f2.wl_matmul(*d, offset_copy(xd, off)))
+        assert np.linalg.norm(y - want) <= bound
+        np.testing.assert_array_equal(y, host(f2.wl_matmul(*d, offset_copy(xd, off))))
+
+
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+def test_float_layer_not_finite(gpu, bad):
+    """An infinite real part reaches only the component that its code's axis
+    feeds (T = 1: one code of U and one of W); an undefined one likewise."""
+    import paper_2512_02901_amd as f2
+    N, K = 7, 20
+    (cu, su, cw, sw), d, rng = layer(N, K, 1, gpu)
+    x = (rng.standard_normal((2, K)) + 1j * rng.standard_normal((2, K))).astype(np.complex64)
+    x.real[1, 13] = bad
+    y = host(f2.wl_matmul(*d, dev(x, gpu)))
+    odd_u, odd_w = cu[0, :, 13] & 1 == 1, cw[0, :, 13] & 1 == 1
+    assert np.isfinite(y[0]).all()
+    # Re x feeds Re y through the real axis (even codes), Im y through the imaginary one
+    np.testing.assert_array_equal(np.isfinite(y[1].real), odd_u & odd_w)
+    np.testing.assert_array_equal(np.isfinite(y[1].imag), ~odd_u & ~odd_w)
