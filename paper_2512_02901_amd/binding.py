@@ -131,14 +131,24 @@ def _check(status: int, where: str):
 
 # --------------------------------------------------------------- helpers ---
 
+_torch_module = None
+_raw_stream = None  # device index -> handle of torch's current stream there
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module, _raw_stream
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+        # the handle alone (0.07 us); torch.cuda.current_stream builds a Stream object for it (1.9 us)
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or \
+            (lambda index: torch.cuda.current_stream(index).cuda_stream)
+    return _torch_module
 
 
 def _stream_ptr(tensor) -> int:
-    torch = _torch()
-    return torch.cuda.current_stream(tensor.device).cuda_stream
+    _torch()
+    return _raw_stream(tensor.get_device())
 
 
 def _ptr(t):
@@ -146,7 +156,7 @@ def _ptr(t):
 
 
 def _require(t, dtype, name, device=None):
-    torch = _torch()
+    torch = _torch_module or _torch()
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if not t.is_cuda:
@@ -347,35 +357,35 @@ def quantize_grouped(M, T: int, G: int):
 
 
 def _act_dtype(x):
-    torch = _torch()
-    if x.dtype == torch.complex64:
+    torch = _torch_module or _torch()
+    dtype = x.dtype
+    if dtype is torch.complex64:
         return ACT_F32
-    if x.dtype == torch.bfloat16:
+    if dtype is torch.bfloat16:
         return ACT_BF16
-    if x.dtype == torch.int8:
+    if dtype is torch.int8:
         return ACT_I8
-    raise TypeError(f"unsupported activation dtype {x.dtype}")
+    raise TypeError(f"unsupported activation dtype {dtype}")
 
 
 def _act_shape(x):
     """(B, K) of an activation tensor: complex64 [B, K] or bf16/int8 [B, K, 2]."""
-    if x.dim() == 2:
-        return x.shape[0], x.shape[1]
-    if x.dim() == 3 and x.shape[2] == 2:
-        return x.shape[0], x.shape[1]
+    shape = x.shape
+    if len(shape) == 2 or (len(shape) == 3 and shape[2] == 2):
+        return shape[0], shape[1]
     raise ValueError("activations must be complex64 [B, K] or bf16/int8 [B, K, 2]")
 
 
 def quantize_act_int8(x):
     """x: complex64 [B, K] or bf16 [B, K, 2] -> (q int8 [B, K, 2], x_scale float32 [B])."""
-    torch = _torch()
-    lib = load()
+    torch = _torch_module or _torch()
+    lib = _lib or load()
     _require(x, None, "x")
     dt = _act_dtype(x)
     B, K = _act_shape(x)
     q = torch.empty((B, K, 2), dtype=torch.int8, device=x.device)
     xs = torch.empty((B,), dtype=torch.float32, device=x.device)
-    _check(lib.fairy2i_quantize_act_int8(_ptr(x), dt, B, K, _ptr(q), _ptr(xs), _stream_ptr(x)),
+    _check(lib.fairy2i_quantize_act_int8(x.data_ptr(), dt, B, K, q.data_ptr(), xs.data_ptr(), _stream_ptr(x)),
            "fairy2i_quantize_act_int8")
     return q, xs
 
@@ -386,13 +396,22 @@ def wl_matmul_workspace_bytes(N, K, T, B, dtype) -> int:
 
 def wl_matmul(codes_U, scales_U, codes_W, scales_W, x, x_scale=None, out=None, workspace=None):
     """y = sum_t U^(t) x + W^(t) conj(x) for each token; complex64 [B, N]."""
-    torch = _torch()
-    lib = load()
-    for t, n in ((codes_U, "codes_U"), (codes_W, "codes_W")):
-        _require(t, torch.uint8, n)
-    for t, n in ((scales_U, "scales_U"), (scales_W, "scales_W")):
-        _require(t, torch.float32, n)
-    _require(x, None, "x")
+    torch = _torch_module or _torch()
+    lib = _lib or load()
+    # Launch latency counts here (a small layer's kernel runs 4 us), so all
+    # operands are first looked over in one expression; _check_wl names what is wrong.
+    try:
+        index = x.get_device()
+        ok = (index >= 0
+              and codes_U.dtype is torch.uint8 and codes_U.get_device() == index and codes_U.is_contiguous()
+              and codes_W.dtype is torch.uint8 and codes_W.get_device() == index and codes_W.is_contiguous()
+              and scales_U.dtype is torch.float32 and scales_U.get_device() == index and scales_U.is_contiguous()
+              and scales_W.dtype is torch.float32 and scales_W.get_device() == index and scales_W.is_contiguous()
+              and x.is_contiguous())
+    except (AttributeError, TypeError):
+        ok = False
+    if not ok:
+        _check_wl(codes_U, scales_U, codes_W, scales_W, x)
     T, N, KB = codes_U.shape
     if codes_W.shape != codes_U.shape or scales_U.shape != (T, 2) or scales_W.shape != (T, 2):
         raise ValueError("codes/scales shapes disagree")
@@ -401,23 +420,37 @@ def wl_matmul(codes_U, scales_U, codes_W, scales_W, x, x_scale=None, out=None, w
     if K != 4 * KB:
         raise ValueError(f"activations have K={K}, codes have K={4 * KB}")
     dev_ = x.device
-    for t, n in ((codes_U, "codes_U"), (codes_W, "codes_W"), (scales_U, "scales_U"), (scales_W, "scales_W")):
-        _require(t, None, n, dev_)
     if x_scale is not None:
         _require(x_scale, torch.float32, "x_scale", dev_)
-        if tuple(x_scale.shape) != (B,):
+        if x_scale.shape != (B,):
             raise ValueError(f"x_scale must have shape ({B},), got {tuple(x_scale.shape)}")
     if out is None:
         out = torch.empty((B, N), dtype=torch.complex64, device=dev_)
     else:
         _require(out, torch.complex64, "out", dev_)
-        if tuple(out.shape) != (B, N):
+        if out.shape != (B, N):
             raise ValueError(f"out must have shape ({B}, {N}), got {tuple(out.shape)}")
-    workspace, wsb = _workspace(lib.fairy2i_wl_matmul_workspace_bytes(N, K, T, B, dt), workspace, dev_)
-    _check(lib.fairy2i_wl_matmul(_ptr(codes_U), _ptr(scales_U), _ptr(codes_W), _ptr(scales_W), T, N, K,
-                                 _ptr(x), _ptr(x_scale), dt, B, _ptr(out), _ptr(workspace), wsb,
-                                 _stream_ptr(x)), "fairy2i_wl_matmul")
+    if workspace is None:
+        workspace, wsb = _workspace(lib.fairy2i_wl_matmul_workspace_bytes(N, K, T, B, dt), None, dev_)
+    else:  # its size is the library's to check
+        _require(workspace, torch.uint8, "workspace", dev_)
+        wsb = workspace.numel()
+    _check(lib.fairy2i_wl_matmul(codes_U.data_ptr(), scales_U.data_ptr(), codes_W.data_ptr(), scales_W.data_ptr(),
+                                 T, N, K, x.data_ptr(), None if x_scale is None else x_scale.data_ptr(), dt, B,
+                                 out.data_ptr(), None if workspace is None else workspace.data_ptr(), wsb,
+                                 _raw_stream(x.get_device())), "fairy2i_wl_matmul")
     return out
+
+
+def _check_wl(codes_U, scales_U, codes_W, scales_W, x):
+    torch = _torch()
+    for t, n in ((codes_U, "codes_U"), (codes_W, "codes_W")):
+        _require(t, torch.uint8, n)
+    for t, n in ((scales_U, "scales_U"), (scales_W, "scales_W")):
+        _require(t, torch.float32, n)
+    _require(x, None, "x")
+    for t, n in ((codes_U, "codes_U"), (codes_W, "codes_W"), (scales_U, "scales_U"), (scales_W, "scales_W")):
+        _require(t, None, n, x.device)
 
 
 NOALLOC_SCRATCH_BYTES = 32 << 20
