@@ -11,21 +11,18 @@
 //                 (angles in double), key and value written to the caches
 //   attn_partial  per (head, 64-position slice): scores, slice max, slice
 //                 softmax sum and the slice's weighted sum of values
-//   attn_combine  the slices of a head merged in slice order, bf16 out
+//   attn_combine  the slices of a head merged in a fixed order, bf16 out
 //   swiglu        silu(Re g) Re u + i silu(Im g) Im u, bf16 out
 //   add           the final residual add
-// For one token on the fp4 path with two digit bands (every block this
-// library plans, up to 8192 complex entries per token) the fused path runs
-// instead: 13 launches in place of 19.  The stage that consumes a
-// projection's output sums that projection's split-K partials itself, and
-// the stage that makes a projection's input writes its activation operand:
-//   operand (norm)  x (+ the o projection's output), RMSNorm, operand of
-//                   q k v (of gate and up)
-//   rope_append_sum q k v summed, rotary embedding, caches
-//   operand (bf16)  operand of a bf16 token (the attention output; SwiGLU's)
-//   swiglu_sum      gate and up summed, SwiGLU, bf16 out
-//   add_sum         down summed, the final residual add
-// so only the product kernels of the four group calls remain of them.
+// For one token with two digit bands (every block this library plans, up to
+// 8192 complex entries per token) the fused path runs instead: six launches
+// in place of 19, one per product with the stages around it inside, and the
+// attention's two:
+//   norm, q k v product, rotary embedding, caches
+//   attention
+//   o product, first residual add
+//   norm, gate and up product, SwiGLU
+//   down product, second residual add
 // Complex vectors are float2 (re, im); a head owns dc = n / n_heads
 // consecutive complex entries (entry j: its real dims j and j + dc).  All
 // reductions run in a fixed order, so results are bitwise reproducible.
@@ -33,7 +30,7 @@
 #include <string.h>
 
 #include "common.h"
-#include "decode.h"
+#include "decode_dev.h"
 #include "f4_operand.h"
 
 namespace fairy2i {
@@ -41,7 +38,7 @@ namespace fairy2i {
 namespace {
 
 constexpr int kAttnSlice = 64;   // positions per attention slice (one per lane)
-constexpr int kMaxAttnSlices = 4096;  // slices per head the combine keeps in LDS
+constexpr int kMaxAttnSlices = 4096;  // slices per head: their factors sit in LDS
 constexpr int kNormThreads = 256;
 
 __device__ inline uint16_t bf16_rne(float f) {
@@ -50,7 +47,8 @@ __device__ inline uint16_t bf16_rne(float f) {
   return (uint16_t)(u >> 16);
 }
 
-__device__ inline float wave_sum(float v) {
+template <typename V>
+__device__ inline V wave_sum(V v) {
   // butterfly: every lane ends with the same, commutatively formed sum
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
   return v;
@@ -58,6 +56,11 @@ __device__ inline float wave_sum(float v) {
 
 __device__ inline float wave_max(float v) {
   for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
+  return v;
+}
+
+__device__ inline double wave_max(double v) {
+  for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off));
   return v;
 }
 
@@ -120,149 +123,207 @@ __global__ void rope_append_kernel(const float2* __restrict__ q, const float2* _
   v_cache[at] = v[i];
 }
 
-// One block of four waves per (64-position slice, head).  Scores: four lanes
-// per position, each taking a quarter of the key row's 16-byte chunks (eight
-// loads in flight), summed across the four lanes, times scale; then the
-// slice's maximum m, e_t = exp(s_t - m) (kept in LDS) and l = sum e_t.
-// Values: wave w takes positions 16 w .. 16 w + 15, lane j (+ 64 r) entry j
-// of o = sum_t e_t v_t (eight value loads in flight), and the four waves'
-// sums are added in wave order.  Partial record per (head, slice):
-// [m, l, o (2 dc floats)].
+// One block of four waves per (64-position slice, head).  Scores: eight lanes
+// per position, which take a key row's 16-byte chunks in turn (128 bytes a
+// row and load, eight loads in flight), summed across the lanes, times scale;
+// then the slice's maximum m, e_t = exp(s_t - m) (kept in LDS) and
+// l = sum e_t.  Values: wave w takes positions 16 w .. 16 w + 15 of
+// o = sum_t e_t v_t, 16 bytes a lane, and the four waves' sums are added in
+// wave order.  From the scores on everything is in double (bound by memory,
+// the kernel has the time): the output is rounded to bf16, and a sum in float
+// puts a value next to a tie on the wrong side about once a token of 2048
+// entries.  Partial record per (head, slice): [m, l, o (2 dc doubles)].
 constexpr int kAttnThreads = 256;
 template <int R>  // complex entries per lane in the value pass: dc <= 64 R
-__global__ __launch_bounds__(kAttnThreads) void attn_partial_kernel(const float2* __restrict__ q_rot,
+__global__ __launch_bounds__(kAttnThreads, R == 1 ? 4 : 2) void attn_partial_kernel(const float2* __restrict__ q_rot,
                                                                     const float2* __restrict__ k_cache,
                                                                     const float2* __restrict__ v_cache, int dc,
-                                                                    int64_t n_ctx, int64_t max_ctx, float scale,
-                                                                    float* __restrict__ part) {
-  __shared__ float es[kAttnSlice];
-  __shared__ float redm[kAttnThreads / 64], redl[kAttnThreads / 64];
-  __shared__ float2 ow[kAttnThreads / 64][64 * R];
+                                                                    int64_t n_ctx, int64_t max_ctx, double scale,
+                                                                    double2* __restrict__ part) {
+  __shared__ double es[kAttnSlice];
+  __shared__ double redm[kAttnThreads / 64], redl[kAttnThreads / 64];
+  __shared__ double2 ow[kAttnThreads / 64][64 * R];
   const int h = blockIdx.y, sl = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t n0 = (int64_t)sl * kAttnSlice;
   const int cnt = (int)min((int64_t)kAttnSlice, n_ctx - n0);
   const float2* kh = k_cache + (int64_t)h * max_ctx * dc;
   const float2* vh = v_cache + (int64_t)h * max_ctx * dc;
   const float4* qh = reinterpret_cast<const float4*>(q_rot + (int64_t)h * dc);
-  const int p = tid >> 2, qd = tid & 3, nf4 = dc / 2;
-  float acc = 0.0f;
-  if (p < cnt) {
-    const float4* kp = reinterpret_cast<const float4*>(kh + (n0 + p) * dc);
-    for (int j0 = qd; j0 < nf4; j0 += 32) {
-      float4 kv[8], qv[8];
+  const int p = tid >> 3, qd = tid & 7, nf4 = dc / 2;
+  double acc[2] = {0.0, 0.0};
+#pragma unroll 1
+  for (int j0 = qd; j0 < nf4; j0 += 32) {
+    float4 kv[2][4], qv[4];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int j = j0 + 4 * u;
-        kv[u] = j < nf4 ? kp[j] : make_float4(0.f, 0.f, 0.f, 0.f);
-        qv[u] = j < nf4 ? qh[j] : make_float4(0.f, 0.f, 0.f, 0.f);
-      }
+    for (int u = 0; u < 4; ++u) {
+      const int j = j0 + 8 * u;
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        acc = fmaf(qv[u].x, kv[u].x, acc);
-        acc = fmaf(qv[u].y, kv[u].y, acc);
-        acc = fmaf(qv[u].z, kv[u].z, acc);
-        acc = fmaf(qv[u].w, kv[u].w, acc);
+      for (int hf = 0; hf < 2; ++hf) {
+        const int t = p + 32 * hf;
+        kv[hf][u] = t < cnt && j < nf4 ? reinterpret_cast<const float4*>(kh + (n0 + t) * dc)[j] : make_float4(0.f, 0.f, 0.f, 0.f);
       }
+      qv[u] = j < nf4 ? qh[j] : make_float4(0.f, 0.f, 0.f, 0.f);
     }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf) {
+        acc[hf] = fma((double)qv[u].x, (double)kv[hf][u].x, acc[hf]);
+        acc[hf] = fma((double)qv[u].y, (double)kv[hf][u].y, acc[hf]);
+        acc[hf] = fma((double)qv[u].z, (double)kv[hf][u].z, acc[hf]);
+        acc[hf] = fma((double)qv[u].w, (double)kv[hf][u].w, acc[hf]);
+      }
   }
-  acc += __shfl_xor(acc, 1);
-  acc += __shfl_xor(acc, 2);
-  const float s = p < cnt ? acc * scale : -INFINITY;
-  float m = wave_max(s);
+  // the first values are asked for before the scores are reduced (all 16
+  // positions; for wide heads four: there are no registers for more)
+  constexpr int LPR = R == 1 ? 32 : 64, RPI = 64 / LPR, NR = R == 1 ? 1 : 2;  // lanes a row, rows and loads of one
+  constexpr int VL = R == 1 ? 8 : 4;
+  const int pb = 16 * wave, vj = lane % LPR, vr = lane / LPR;
+  float4 vv[VL][NR];
+  auto load_values = [&](int t0) {
+#pragma unroll
+    for (int u = 0; u < VL; ++u)
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        const int t = pb + t0 + u * RPI + vr, j = vj + LPR * r;
+        vv[u][r] = t < cnt && j < nf4 ? reinterpret_cast<const float4*>(vh + (n0 + t) * dc)[j] : make_float4(0.f, 0.f, 0.f, 0.f);
+      }
+  };
+  load_values(0);
+  double s[2];
+#pragma unroll
+  for (int hf = 0; hf < 2; ++hf) {
+    acc[hf] += __shfl_xor(acc[hf], 1);
+    acc[hf] += __shfl_xor(acc[hf], 2);
+    acc[hf] += __shfl_xor(acc[hf], 4);
+    s[hf] = p + 32 * hf < cnt ? acc[hf] * scale : -INFINITY;
+  }
+  double m = wave_max(fmax(s[0], s[1]));
   if (lane == 0) redm[wave] = m;
   __syncthreads();
-  m = fmaxf(fmaxf(redm[0], redm[1]), fmaxf(redm[2], redm[3]));
-  const float e = p < cnt ? expf(s - m) : 0.0f;
-  if (qd == 0) es[p] = e;
-  const float lw = wave_sum(qd == 0 ? e : 0.0f);
+  m = fmax(fmax(redm[0], redm[1]), fmax(redm[2], redm[3]));
+  double lw = 0.0;
+#pragma unroll
+  for (int hf = 0; hf < 2; ++hf) {
+    const double e = p + 32 * hf < cnt ? exp(s[hf] - m) : 0.0;
+    if (qd == 0) {
+      es[p + 32 * hf] = e;
+      lw += e;
+    }
+  }
+  lw = wave_sum(lw);
   if (lane == 0) redl[wave] = lw;
   __syncthreads();
-  const float l = ((redl[0] + redl[1]) + redl[2]) + redl[3];
-  float2 o[R];
+  const double l = ((redl[0] + redl[1]) + redl[2]) + redl[3];
+  double o[NR][4];
 #pragma unroll
-  for (int r = 0; r < R; ++r) o[r] = make_float2(0.f, 0.f);
-  const int pb = 16 * wave;
+  for (int r = 0; r < NR; ++r) o[r][0] = o[r][1] = o[r][2] = o[r][3] = 0.0;
+#pragma unroll 1
+  for (int t0 = 0; t0 < 16; t0 += VL * RPI) {
+    if (t0 > 0) load_values(t0);
 #pragma unroll
-  for (int t0 = 0; t0 < 16; t0 += 8) {
-    float2 vv[8][R];
+    for (int u = 0; u < VL; ++u) {
+      const double w = es[pb + t0 + u * RPI + vr];  // 0 past cnt
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int t = pb + t0 + u, j = lane + 64 * r;
-        vv[u][r] = (t < cnt && j < dc) ? vh[(n0 + t) * dc + j] : make_float2(0.f, 0.f);
-      }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const float w = es[pb + t0 + u];  // 0 past cnt
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        o[r].x = fmaf(w, vv[u][r].x, o[r].x);
-        o[r].y = fmaf(w, vv[u][r].y, o[r].y);
+      for (int r = 0; r < NR; ++r) {
+        o[r][0] = fma(w, (double)vv[u][r].x, o[r][0]);
+        o[r][1] = fma(w, (double)vv[u][r].y, o[r][1]);
+        o[r][2] = fma(w, (double)vv[u][r].z, o[r][2]);
+        o[r][3] = fma(w, (double)vv[u][r].w, o[r][3]);
       }
     }
   }
 #pragma unroll
-  for (int r = 0; r < R; ++r) ow[wave][lane + 64 * r] = o[r];
-  __syncthreads();
-  float* rec = part + ((int64_t)h * gridDim.x + sl) * (2 + 2 * dc);
-  if (tid == 0) {
-    rec[0] = m;
-    rec[1] = l;
+  for (int r = 0; r < NR; ++r) {
+    if constexpr (RPI == 2) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) o[r][k] += __shfl_xor(o[r][k], 32);
+    }
+    if (vr == 0) {
+      ow[wave][2 * (vj + LPR * r)] = make_double2(o[r][0], o[r][1]);
+      ow[wave][2 * (vj + LPR * r) + 1] = make_double2(o[r][2], o[r][3]);
+    }
   }
+  __syncthreads();
+  double2* rec = part + ((int64_t)h * gridDim.x + sl) * (1 + dc);
+  if (tid == 0) rec[0] = make_double2(m, l);
   for (int j = tid; j < dc; j += kAttnThreads) {
-    float2 a = ow[0][j];
+    double2 a = ow[0][j];
     for (int w = 1; w < kAttnThreads / 64; ++w) {
       a.x += ow[w][j].x;
       a.y += ow[w][j].y;
     }
-    rec[2 + 2 * j] = a.x;
-    rec[3 + 2 * j] = a.y;
+    rec[1 + j] = a;
   }
 }
 
-// Per head: M = max_s m_s, f_s = e^(m_s - M) (kept in LDS), L = sum_s l_s f_s,
-// o_j = sum_s o_{s,j} f_s / L over the slices in order; written as bf16 pairs
-// at the head's entries.
-__global__ __launch_bounds__(64) void attn_combine_kernel(const float* __restrict__ part, int n_slices, int dc,
-                                                          uint16_t* __restrict__ o_out) {
-  __shared__ float fs[kMaxAttnSlices];
-  const int h = blockIdx.x, lane = threadIdx.x;
-  const int rl = 2 + 2 * dc;
-  const float* ph = part + (int64_t)h * n_slices * rl;
-  float M = -INFINITY;
-  for (int sl = lane; sl < n_slices; sl += 64) M = fmaxf(M, ph[(int64_t)sl * rl]);
-  M = wave_max(M);
-  float L = 0.0f;
-  for (int s0 = 0; s0 < n_slices; s0 += 64) {
-    const int sl = s0 + lane;
-    float f = 0.0f, t = 0.0f;
-    if (sl < n_slices) {
-      f = expf(ph[(int64_t)sl * rl] - M);
-      t = ph[(int64_t)sl * rl + 1] * f;
-      fs[sl] = f;
-    }
-    L += wave_sum(t);
-  }
-  __syncthreads();
-  const float invL = 1.0f / L;
-  for (int j = lane; j < dc; j += 64) {
-    float ore = 0.0f, oim = 0.0f;
-    for (int s0 = 0; s0 < n_slices; s0 += 8) {
-      float2 ov[8];
+// Per head: M = max_s m_s, f_s = e^(m_s - M) (in LDS), L = sum_s l_s f_s,
+// o_j = sum_s o_{s,j} f_s / L, wave w adding slices w, w + 4, ... and the
+// waves' sums added in wave order; written as bf16 pairs at the head's
+// entries.  (A kernel of its own: merged by the block that ends last for its
+// head, every slice's block waits for its record and for its count, 18.4 us
+// at context 2048 and 36.3 at 4096 in all, against 14.2 + 4.7 and 25.4 + 4.7.)
+template <int R>
+__global__ __launch_bounds__(kAttnThreads) void attn_combine_kernel(const double2* __restrict__ part, int ns, int dc,
+                                                                    uint32_t* __restrict__ o_out) {
+  extern __shared__ double fs[];
+  __shared__ double redm[kAttnThreads / 64], redl[kAttnThreads / 64];
+  __shared__ double2 ow[kAttnThreads / 64][64 * R];
+  const int h = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int rl = 1 + dc;
+  const double2* ph = part + (int64_t)h * ns * rl;
+  // every wave's first eight slices (of an entry a lane) and every thread's
+  // first (m, l) in one round of loads
+  double2 ov[8];
+  auto load_slices = [&](int i0, int r) {
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
-        ov[u] = s0 + u < n_slices ? *reinterpret_cast<const float2*>(ph + (int64_t)(s0 + u) * rl + 2 + 2 * j)
-                                  : make_float2(0.f, 0.f);
+    for (int u = 0; u < 8; ++u) {
+      const int i = i0 + 4 * u, j = lane + 64 * r;
+      ov[u] = i < ns && j < dc ? ph[(int64_t)i * rl + 1 + j] : make_double2(0.0, 0.0);
+    }
+  };
+  const double2 ml0 = tid < ns ? ph[(int64_t)tid * rl] : make_double2(-INFINITY, 0.0);
+  load_slices(wave, 0);
+  double M = ml0.x;
+  for (int i = tid + kAttnThreads; i < ns; i += kAttnThreads) M = fmax(M, ph[(int64_t)i * rl].x);
+  M = wave_max(M);
+  if (lane == 0) redm[wave] = M;
+  __syncthreads();
+  M = fmax(fmax(redm[0], redm[1]), fmax(redm[2], redm[3]));
+  double lt = 0.0;
+  for (int i = tid; i < ns; i += kAttnThreads) {
+    const double2 ml = i == tid ? ml0 : ph[(int64_t)i * rl];
+    const double f = exp(ml.x - M);
+    fs[i] = f;
+    lt = fma(ml.y, f, lt);
+  }
+  lt = wave_sum(lt);
+  if (lane == 0) redl[wave] = lt;
+  __syncthreads();
+  const double L = ((redl[0] + redl[1]) + redl[2]) + redl[3];
+#pragma unroll 1
+  for (int r = 0; r < R; ++r) {
+    double2 a = make_double2(0.0, 0.0);
+    for (int i0 = wave; i0 < ns; i0 += 32) {
+      if (r > 0 || i0 != wave) load_slices(i0, r);
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        const float f = s0 + u < n_slices ? fs[s0 + u] : 0.0f;
-        ore = fmaf(ov[u].x, f, ore);
-        oim = fmaf(ov[u].y, f, oim);
+        const int i = i0 + 4 * u;
+        const double f = i < ns ? fs[i] : 0.0;
+        a.x = fma(ov[u].x, f, a.x);
+        a.y = fma(ov[u].y, f, a.y);
       }
     }
-    o_out[2 * (h * dc + j)] = bf16_rne(ore * invL);
-    o_out[2 * (h * dc + j) + 1] = bf16_rne(oim * invL);
+    ow[wave][lane + 64 * r] = a;
+  }
+  __syncthreads();
+  for (int j = tid; j < dc; j += kAttnThreads) {
+    double2 a = ow[0][j];
+    for (int w = 1; w < kAttnThreads / 64; ++w) {
+      a.x += ow[w][j].x;
+      a.y += ow[w][j].y;
+    }
+    o_out[h * dc + j] = (uint32_t)bf16_rne((float)(a.x / L)) | ((uint32_t)bf16_rne((float)(a.y / L)) << 16);
   }
 }
 
@@ -286,269 +347,305 @@ __global__ void add_kernel(const float2* __restrict__ a, const float2* __restric
 }
 
 // ---------------------------------------------------------- fused path ---
-// For one token on the fp4 path (two digit bands, one 8-column tile), the
-// block's elementwise stages also do the grouped call's other two launches:
-// the kernel that needs a layer's output sums that layer's split-K partials
-// itself (in slice order, the additions of the grouped call's reduction),
-// and the stage that makes a projection's input also writes that
-// projection's activation operand (token shift, digit pairs; f4_operand.h).
-
-// A projection's output: its split-K partials [nkc][N] or, with one slice,
-// the output itself.
-struct LayerOut {
-  const float2* part;
+// One product per launch, the stages around it inside.  What bounds a block
+// of one token is latency: its codes (50 MB at n = 2048, n_ff = 5504, T = 2)
+// and 2048 cached positions (67 MB) take 20 us at the rate of a large copy,
+// while each launch of a chain costs 4-7 us whatever it does.  So a thread
+// block owns 16 rows of a projection (of gate and of up for SwiGLU: M = 2
+// matrices), its waves split K in 256-code steps (wave w of a matrix takes
+// steps w, w + KW, ...) and add their shares of y in LDS, in double and in
+// wave order; nothing is left for a reduction, and what follows the row
+// (rotary embedding and caches, residual add, SwiGLU) is done by the thread
+// that holds it.  The token is formed by every block: RMSNorm of x (the same
+// fixed order in each) or the bf16 token as it stands; a wave then encodes
+// the digits of its own steps (f4_operand.h), a lane per half run and
+// component, while its codes, asked for before all this, arrive.  What is
+// rounded to bf16 (the tokens, SwiGLU) is computed in double up to there,
+// from the digits' sums on: the fewer roundings, the fewer values fall on the
+// other side of a tie (products against 64 bits 6.5e-8 -> 2.5e-8).
+// One token at the sizes above: 13 launches 78.6 us, now 51.7; the products
+// with their stages 10.2 (q k v), 5.1 (o), 12.4 (gate, up) and 8.0 (down).
+struct SplitMatrix {
+  const uint8_t* codes[2];  // U, W, fp4 tiled
+  const float* scales[2];
   float2* y;
-  int32_t nkc, N;
 };
 
-// Entry i of NS projections' outputs: each output's slices added in order
-// from +0 (the additions of the grouped call's reduction), the loads of U
-// slices of every output in flight together; summed outputs are also written
-// where that reduction would write them.
-template <int NS, int U = 8>
-__device__ inline void layer_outs(const LayerOut (&o)[NS], int i, float2 (&r)[NS]) {
-  int mk = 1;
-#pragma unroll
-  for (int q = 0; q < NS; ++q) {
-    mk = max(mk, o[q].nkc);
-    r[q] = make_float2(0.0f, 0.0f);
-  }
-  for (int kc0 = 0; kc0 < mk; kc0 += U) {
-    float2 t[NS][U];
-#pragma unroll
-    for (int q = 0; q < NS; ++q)
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int kc = kc0 + u;
-        t[q][u] = o[q].nkc > 1 ? (kc < o[q].nkc ? o[q].part[(int64_t)kc * o[q].N + i] : make_float2(0.f, 0.f))
-                               : (kc == 0 ? o[q].y[i] : make_float2(0.f, 0.f));
-      }
-#pragma unroll
-    for (int q = 0; q < NS; ++q)
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (kc0 + u < max(o[q].nkc, 1)) {
-          r[q].x += t[q][u].x;
-          r[q].y += t[q][u].y;
-        }
-  }
-#pragma unroll
-  for (int q = 0; q < NS; ++q)
-    if (o[q].nkc > 1) o[q].y[i] = r[q];
-}
-
-// Up to three projections fed the same token: their operand buffers and
-// output factors, the operand's 256-code steps and the claim counter of
-// their group call (zeroed for the product kernel, as the grouped call's
-// own operand kernel does).
-struct OperandTargets {
-  int8_t* xf[3];
-  float* xs[3];
-  int32_t count, nk4;
-  uint32_t* ctr;
-};
-
-constexpr int kOpThreads = 512;
-constexpr int kOpMaxK = 16 * kOpThreads;  // complex entries of a token the operand kernel takes
-constexpr int kSrcNorm = 0, kSrcBf16 = 1;
-
-struct OperandArgs {
-  int32_t K;  // complex entries of the token
-  // kSrcNorm: v = x (+ the residual branch res); h_out = v; z = RMSNorm(v) gamma
+struct SplitArgs {
+  int32_t K, nk4, N;
+  uint32_t code_bytes;  // of one matrix's codes
+  SplitMatrix m[3];
+  // kSrcNorm: the token z = bf16(x / sqrt(mean |x|^2 + eps) gamma); kSrcBf16: tok
   const float2* x;
-  LayerOut res;      // res.y null: no residual branch
-  float2* h_out;
   const float* gamma;
   float eps;
-  uint16_t* z_out;  // the bf16 token
-  // kSrcBf16: the token as bf16 (re, im) words
+  uint32_t* z_out;
   const uint32_t* tok;
-  OperandTargets t;
+  // kOutRope
+  const double* theta;
+  int64_t pos, max_ctx;
+  int32_t dc;
+  float2 *q_rot, *k_cache, *v_cache;
+  // kOutAdd: sum = base + y
+  const float2* base;
+  float2* sum;
+  // kOutSwiglu
+  uint32_t* act;
 };
 
-// Entries tid + e kOpThreads (e < E) of a projection's output, every load of
-// U slices in flight together; the slices are added in order.
-template <int E>
-__device__ inline void gather_out(const LayerOut& o, int tid, int K, float2 (&acc)[E]) {
-  constexpr int U = E <= 4 ? 8 : (E <= 8 ? 4 : 2);
-#pragma unroll
-  for (int e = 0; e < E; ++e) acc[e] = make_float2(0.0f, 0.0f);
-  if (o.nkc <= 1) {
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int i = tid + e * kOpThreads;
-      if (i < K) acc[e] = o.y[i];
-    }
-    return;
-  }
-  for (int kc0 = 0; kc0 < o.nkc; kc0 += U) {
-    float2 t[U][E];
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        const int i = tid + e * kOpThreads;
-        t[u][e] = (kc0 + u < o.nkc && i < K) ? o.part[(int64_t)(kc0 + u) * o.N + i] : make_float2(0.0f, 0.0f);
-      }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (kc0 + u < o.nkc)
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-          acc[e].x += t[u][e].x;
-          acc[e].y += t[u][e].y;
-        }
-  }
-  // the sums start from +0 and add the slices in order, as the grouped
-  // call's reduction does; write them where that reduction would
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int i = tid + e * kOpThreads;
-    if (i < K) o.y[i] = acc[e];
-  }
-}
+constexpr int kSrcNorm = 0, kSrcBf16 = 1;
+constexpr int kOutRope = 0, kOutAdd = 1, kOutSwiglu = 2;
+constexpr int kSplitMaxK = 8192;  // complex entries of a token the fused path takes
 
-// One block: the token's bf16 words in LDS (entry i of thread i mod
-// kOpThreads, E entries a thread: K <= E kOpThreads), their largest
-// magnitude, then the digits of every half run (8 codes) of the operand
-// (runs past K hold zeros) for each target.
-template <int SRC, int E>
-__global__ __launch_bounds__(kOpThreads) void block_operand_kernel(OperandArgs a) {
-  __shared__ __align__(16) uint32_t tokw[E * kOpThreads];
-  __shared__ float red[kOpThreads / 64];
-  __shared__ float sh_g;
-  const int K = a.K, tid = threadIdx.x, wave = tid >> 6;
+// M matrices with KW waves each; a token of K <= E * threads entries.
+template <int T, int KW, int M, int SRC, int OUT, int E>
+__global__ __launch_bounds__(64 * KW * M) void block_product_kernel(SplitArgs a) {
+#if defined(__HIP_DEVICE_COMPILE__)  // buffer-descriptor code: device pass only
+  constexpr int P = 2 * T, W = KW * M, NTH = 64 * W;
+  __shared__ __attribute__((aligned(16))) uint32_t tokw[E * NTH];
+  __shared__ __attribute__((aligned(16))) uint8_t xop[W][16 * 8 * 16];  // a step's operand: [run][column][16 bytes]
+  __shared__ double red[W];
+  __shared__ float redm[W];
+  __shared__ double part[W][2][17];  // [wave][component][row]
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, li = lane & 15;
+  const int wave = uniform(tid >> 6);
+  const int mat = OUT == kOutRope ? (int)blockIdx.y : (M == 2 ? wave / KW : 0);
+  const int kw = wave % KW;
+  const int rb = blockIdx.x, K = a.K;
+  const bool first = blockIdx.x == 0 && blockIdx.y == 0;
+
+  // theta first: its wait then leaves the loads below in flight
+  double theta = 0.0;
+  if constexpr (OUT == kOutRope) {
+    if (tid < 32 && mat < 2) theta = a.theta[(rb * 16 + li) % a.dc];
+  }
+  const __amdgpu_buffer_rsrc_t ru = make_rsrc(uniform_ptr(a.m[mat].codes[0]), a.code_bytes);
+  const __amdgpu_buffer_rsrc_t rw = make_rsrc(uniform_ptr(a.m[mat].codes[1]), a.code_bytes);
+  auto load = [&](int s, v4i(&c)[P]) {  // a step past the last reads zeros
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      const uint32_t off = s < a.nk4 ? (uint32_t)((rb * a.nk4 + s) * T + t) * 1024u + 16u * (uint32_t)lane : kOob;
+      c[t] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(ru, off, 0, kNonTemporal));
+      c[T + t] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rw, off, 0, kNonTemporal));
+    }
+  };
   uint32_t zw[E];
+  float2 v[E];
   if constexpr (SRC == kSrcNorm) {
-    float2 v[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-      const int i = tid + e * kOpThreads;
+      const int i = tid + e * NTH;
       v[e] = i < K ? a.x[i] : make_float2(0.0f, 0.0f);
     }
-    if (a.res.y) {
-      float2 w[E];
-      gather_out<E>(a.res, tid, K, w);
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        v[e].x += w[e].x;
-        v[e].y += w[e].y;
-      }
-    }
-    float ss = 0.0f;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      ss = fmaf(v[e].x, v[e].x, ss);
-      ss = fmaf(v[e].y, v[e].y, ss);
-    }
-    ss = wave_sum(ss);
-    if ((tid & 63) == 0) red[wave] = ss;
-    __syncthreads();
-    float tot = 0.0f;
-    for (int w = 0; w < kOpThreads / 64; ++w) tot += red[w];
-    const float r = 1.0f / sqrtf(tot / (float)(2 * K) + a.eps);
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int i = tid + e * kOpThreads;
-      zw[e] = 0u;
-      if (i < K) {
-        if (a.h_out) a.h_out[i] = v[e];
-        zw[e] = (uint32_t)bf16_rne((v[e].x * r) * a.gamma[i]) | ((uint32_t)bf16_rne((v[e].y * r) * a.gamma[K + i]) << 16);
-      }
-    }
-    __syncthreads();  // red is reused below
   } else {
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-      const int i = tid + e * kOpThreads;
+      const int i = tid + e * NTH;
       zw[e] = i < K ? a.tok[i] : 0u;
     }
   }
-  float m = 0.0f;
+  // gains with the token where the registers allow it; the residual
+  constexpr bool kGainsFirst = SRC == kSrcNorm && E <= 4;
+  float2 ga[kGainsFirst ? E : 1];
+  if constexpr (kGainsFirst) {
 #pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int i = tid + e * kOpThreads;
-    if (i < K) {
-      tokw[i] = zw[e];
-      if constexpr (SRC == kSrcNorm) reinterpret_cast<uint32_t*>(a.z_out)[i] = zw[e];
-      m = fmaxf(m, fmaxf(fabsf(__uint_as_float(zw[e] << 16)), fabsf(__uint_as_float(zw[e] & 0xFFFF0000u))));
+    for (int e = 0; e < E; ++e) {
+      const int i = tid + e * NTH;
+      ga[e] = i < K ? make_float2(a.gamma[i], a.gamma[K + i]) : make_float2(0.0f, 0.0f);
     }
   }
-  m = wave_max(m);
-  if ((tid & 63) == 0) red[wave] = m;
+  float base = 0.0f;  // of row li, component g (lanes 0 .. 31 write the outputs)
+  if constexpr (OUT == kOutAdd) {
+    if (tid < 32) base = reinterpret_cast<const float*>(a.base)[2 * (rb * 16 + li) + g];
+  }
+  v4i c[P];
+  load(kw, c);
+  float sc[2][T][2];  // one wait for the scalar loads, the vector loads in flight
+  sload_scales<T>(uniform_ptr(a.m[mat].scales[0]), uniform_ptr(a.m[mat].scales[1]), sc);
+  double cs = 0.0, sn = 0.0;
+  if constexpr (OUT == kOutRope) {
+    if (tid < 32 && mat < 2) sincos((double)a.pos * theta, &sn, &cs);
+  }
+  if constexpr (SRC == kSrcNorm) {
+    // a thread's few squares in float, the rest and the root in double
+    float s0 = 0.0f;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      s0 = fmaf(v[e].x, v[e].x, s0);
+      s0 = fmaf(v[e].y, v[e].y, s0);
+    }
+    const double ss = wave_sum((double)s0);
+    if (lane == 0) red[wave] = ss;
+    __syncthreads();
+    double tot = 0.0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) tot += red[w];
+    const double ms = tot / (double)(2 * K) + (double)a.eps;
+    const double r0 = (double)(1.0f / sqrtf((float)ms));
+    const double r = r0 > 0.0 && isfinite(r0) ? r0 * (1.5 - 0.5 * ms * r0 * r0) : r0;  // one Newton step
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int i = tid + e * NTH;
+      zw[e] = 0u;
+      if (i < K) {
+        const float2 gn = kGainsFirst ? ga[kGainsFirst ? e : 0] : make_float2(a.gamma[i], a.gamma[K + i]);
+        zw[e] = (uint32_t)bf16_rne((float)((double)v[e].x * r * (double)gn.x)) |
+                ((uint32_t)bf16_rne((float)((double)v[e].y * r * (double)gn.y)) << 16);
+        if (first) a.z_out[i] = zw[e];
+      }
+    }
+  }
+  float gm = 0.0f;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    tokw[tid + e * NTH] = zw[e];
+    gm = fmaxf(gm, fmaxf(fabsf(__uint_as_float(zw[e] << 16)), fabsf(__uint_as_float(zw[e] & 0xFFFF0000u))));
+  }
+  gm = wave_max(gm);
+  if (lane == 0) redm[wave] = gm;
   __syncthreads();
-  if (tid == 0) {
-    float g = 0.0f;
-    for (int w = 0; w < kOpThreads / 64; ++w) g = fmaxf(g, red[w]);
-    sh_g = g;
+  gm = redm[0];
+#pragma unroll
+  for (int w = 1; w < W; ++w) gm = fmaxf(gm, redm[w]);
+  const int S = f4_token_shift(gm);
+
+  v4f aS[P], aI[P];
+#pragma unroll
+  for (int p = 0; p < P; ++p) aS[p] = aI[p] = v4f{0.f, 0.f, 0.f, 0.f};
+  for (int s = kw; s < a.nk4; s += KW) {
+    v4i cn[P];
+    load(s + KW, cn);
+    {
+      const int hr = lane >> 1, comp = lane & 1, k0 = 256 * s + 8 * hr;
+      uint32_t w8[8] = {};
+      if (k0 < K) {  // K % 64 == 0: the half run is in range or past K entirely
+        const uint4 p0 = *reinterpret_cast<const uint4*>(&tokw[k0]);
+        const uint4 p1 = *reinterpret_cast<const uint4*>(&tokw[k0 + 4]);
+        w8[0] = p0.x; w8[1] = p0.y; w8[2] = p0.z; w8[3] = p0.w;
+        w8[4] = p1.x; w8[5] = p1.y; w8[6] = p1.z; w8[7] = p1.w;
+      }
+      float xv[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) xv[e] = __uint_as_float(comp ? (w8[e] & 0xFFFF0000u) : (w8[e] << 16));
+      uint32_t out[2][2][2];
+      f4_unit_digits(xv, S, 2, out);
+      f4_store_unit(xop[wave], hr >> 1, 8, 0, comp, hr & 1, 2, out);
+    }
+    __builtin_amdgcn_wave_barrier();  // the wave's own LDS: written above, read below, in order
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+      v4i x0 = v4i{0, 0, 0, 0}, x1 = x0;
+      if (li < 8) {  // columns 8 .. 15 hold no token
+        x0 = *reinterpret_cast<const v4i*>(&xop[wave][((8 * kb + g) * 8 + li) * 16]);
+        x1 = *reinterpret_cast<const v4i*>(&xop[wave][((8 * kb + 4 + g) * 8 + li) * 16]);
+      }
+      const v8i xa = v8i{x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        v8i bs, bi;
+        expand_f4((uint32_t)c[p][2 * kb], (uint32_t)c[p][2 * kb + 1], bs, bi);
+        aS[p] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(xa, bs, aS[p], kFmtFp8, kFmtFp4, 0, 0, 0, 0);
+        aI[p] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(xa, bi, aI[p], kFmtFp8, kFmtFp4, 0, 0, 0, 0);
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int p = 0; p < P; ++p) c[p] = cn[p];
+  }
+
+  // the wave's share of y (before the token factor): lane group 0 holds the
+  // first band's digits of row li, group 1 the second's (times 2^8); what
+  // follows is linear, so each group forms its share and they are added last
+  {
+    double yr = 0.0, yi = 0.0;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      double re[2][2], im[2][2];  // [matrix][component]: products with b_re = S - I and b_im = I
+#pragma unroll
+      for (int mm = 0; mm < 2; ++mm)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const int p = mm * T + t;
+          const double vS = fma((double)aS[p][2 + k], 1.0 / kLoScale, (double)aS[p][k]);
+          im[mm][k] = fma((double)aI[p][2 + k], 1.0 / kLoScale, (double)aI[p][k]);
+          re[mm][k] = vS - im[mm][k];
+        }
+      const double u_re = sc[0][t][0], u_im = sc[0][t][1], w_re = sc[1][t][0], w_im = sc[1][t][1];
+      yr = fma(u_re, re[0][0], yr);
+      yr = fma(-u_im, im[0][1], yr);
+      yr = fma(w_re, re[1][0], yr);
+      yr = fma(w_im, im[1][1], yr);
+      yi = fma(u_re, re[0][1], yi);
+      yi = fma(u_im, im[0][0], yi);
+      yi = fma(-w_re, re[1][1], yi);
+      yi = fma(w_im, im[1][0], yi);
+    }
+    yr = fma(__shfl_down(yr, 16), 1.0 / kBand2Scale, yr);
+    yi = fma(__shfl_down(yi, 16), 1.0 / kBand2Scale, yi);
+    if (lane < 16) {  // zero for a wave without steps
+      part[wave][0][li] = yr;
+      part[wave][1][li] = yi;
+    }
   }
   __syncthreads();
-  const float g = sh_g;
-  const int S = f4_token_shift(g);
-  if (tid == 0) {
-    for (int t = 0; t < a.t.count; ++t) a.t.xs[t][0] = g > 0.0f ? ldexpf(1.0f, -S) : 0.0f;
-    if (a.t.ctr) *a.t.ctr = 0u;
+  if (tid >= 32) return;
+  const int row = rb * 16 + li;  // N % 64 == 0: every row of the block exists; this lane's component is g
+  const double f = gm > 0.0f ? (double)ldexpf(1.0f, -S) : 0.0;
+  double y[M];
+#pragma unroll
+  for (int q = 0; q < M; ++q) {
+    y[q] = 0.0;
+#pragma unroll
+    for (int w = 0; w < KW; ++w) y[q] += part[q * KW + w][g][li];
+    y[q] *= f;
+    reinterpret_cast<float*>(a.m[M == 2 ? q : mat].y)[2 * row + g] = (float)y[q];
   }
-  uint8_t* const dst[3] = {reinterpret_cast<uint8_t*>(a.t.xf[0]), reinterpret_cast<uint8_t*>(a.t.xf[1]),
-                           reinterpret_cast<uint8_t*>(a.t.xf[2])};
-  f4_encode_token<kOpThreads, 3>(tokw, K, S, a.t.nk4, dst, a.t.count);
+  if constexpr (OUT == kOutRope) {
+    const double other = __shfl_xor(y[0], 16);
+    const float rot = (float)(g == 0 ? y[0] * cs - other * sn : other * sn + y[0] * cs);
+    const int h = row / a.dc;
+    const int64_t at = 2 * (((int64_t)h * a.max_ctx + a.pos) * a.dc + (row - h * a.dc)) + g;
+    if (mat == 0) reinterpret_cast<float*>(a.q_rot)[2 * row + g] = rot;
+    else if (mat == 1) reinterpret_cast<float*>(a.k_cache)[at] = rot;
+    else reinterpret_cast<float*>(a.v_cache)[at] = (float)y[0];
+  } else if constexpr (OUT == kOutAdd) {
+    reinterpret_cast<float*>(a.sum)[2 * row + g] = (float)((double)base + y[0]);
+  } else {
+    reinterpret_cast<uint16_t*>(a.act)[2 * row + g] = bf16_rne((float)(y[0] / (1.0 + exp(-y[0])) * y[M - 1]));
+  }
+#endif
 }
 
-template <int SRC>
-void launch_operand(const OperandArgs& a, hipStream_t s) {
-  const dim3 g(1), b(kOpThreads);
-  if (a.K <= 4 * kOpThreads) hipLaunchKernelGGL((block_operand_kernel<SRC, 4>), g, b, 0, s, a);
-  else if (a.K <= 8 * kOpThreads) hipLaunchKernelGGL((block_operand_kernel<SRC, 8>), g, b, 0, s, a);
-  else hipLaunchKernelGGL((block_operand_kernel<SRC, 16>), g, b, 0, s, a);
+// Waves per matrix: 8 (a step of 256 codes each up to K = 2048); 4 for the
+// two matrices of SwiGLU, so that two blocks fit a CU (with 8 each one does,
+// and 344 blocks take two rounds: 16.2 us against 11.4); 16 where K is
+// longer and one matrix's rows leave most of the chip idle (8 at T = 4, whose
+// sums take the registers).  The token takes E entries a thread.
+template <int T, int SRC, int OUT>
+void launch_block_product(const SplitArgs& a, hipStream_t s) {
+  constexpr int KW = OUT == kOutSwiglu ? 4 : 8, M = OUT == kOutSwiglu ? 2 : 1, KL = OUT == kOutAdd && T <= 3 ? 16 : KW;
+  const dim3 grid((unsigned)(a.N / 16), OUT == kOutRope ? 3 : 1);
+  if (a.K <= 2048)
+    hipLaunchKernelGGL((block_product_kernel<T, KW, M, SRC, OUT, 4>), grid, dim3(512), 0, s, a);
+  else
+    hipLaunchKernelGGL((block_product_kernel<T, KL, M, SRC, OUT, kSplitMaxK / (64 * KL * M)>), grid, dim3(64 * KL * M), 0, s, a);
 }
 
-// rope_append_kernel on the summed q, k and v partials (also written out).
-__global__ void rope_append_sum_kernel(LayerOut q, LayerOut k, LayerOut v, int n, int dc, int64_t pos,
-                                       int64_t max_ctx, double base, float2* __restrict__ q_rot,
-                                       float2* __restrict__ k_cache, float2* __restrict__ v_cache) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const LayerOut o[3] = {q, k, v};
-  float2 r[3];
-  layer_outs<3>(o, i, r);
-  const float2 qv = r[0], kv = r[1], vv = r[2];
-  const int h = i / dc, j = i - h * dc;
-  const double ang = (double)pos * pow(base, -2.0 * (double)j / (double)(2 * dc));
-  double s, c;
-  sincos(ang, &s, &c);
-  const float cf = (float)c, sf = (float)s;
-  q_rot[i] = make_float2(fmaf(qv.x, cf, -qv.y * sf), fmaf(qv.x, sf, qv.y * cf));
-  const int64_t at = ((int64_t)h * max_ctx + pos) * dc + j;
-  k_cache[at] = make_float2(fmaf(kv.x, cf, -kv.y * sf), fmaf(kv.x, sf, kv.y * cf));
-  v_cache[at] = vv;
-}
-
-// out = h1 + d, d summed from its partials (and written out).
-__global__ void add_sum_kernel(const float2* __restrict__ h1, LayerOut d, int n, float2* __restrict__ out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const LayerOut o[1] = {d};
-  float2 r[1];
-  layer_outs<1, 24>(o, i, r);
-  const float2 av = h1[i], bv = r[0];
-  out[i] = make_float2(av.x + bv.x, av.y + bv.y);
-}
-
-// act = bf16(silu(g) u) per component, g and u summed from their partials
-// (and written out).
-__global__ void swiglu_sum_kernel(LayerOut g, LayerOut u, int n, uint32_t* __restrict__ act) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const LayerOut o[2] = {g, u};
-  float2 r[2];
-  layer_outs<2>(o, i, r);
-  act[i] = (uint32_t)bf16_rne(silu(r[0].x) * r[1].x) | ((uint32_t)bf16_rne(silu(r[0].y) * r[1].y) << 16);
+template <int SRC, int OUT>
+void launch_block_product(const SplitArgs& a, int T, hipStream_t s) {
+  switch (T) {
+    case 1: launch_block_product<1, SRC, OUT>(a, s); break;
+    case 2: launch_block_product<2, SRC, OUT>(a, s); break;
+    case 3: launch_block_product<3, SRC, OUT>(a, s); break;
+    default: launch_block_product<4, SRC, OUT>(a, s); break;
+  }
 }
 
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
-// Plan: header, then the four group tables (q k v; o; gate up; down).
-constexpr uint32_t kBlockMagic = 0xFA11B10Cu;
+// Plan: header, rotary frequencies, then the four group tables (q k v; o;
+// gate up; down).
+constexpr uint32_t kBlockMagic = 0xFA11B10Du;
 constexpr int kGroups = 4;
 struct BlockPlanHeader {
   uint32_t magic, abi;
@@ -562,13 +659,14 @@ struct BlockPlanHeader {
   // workspace buffers
   uint16_t* z;
   float2 *q, *k, *v, *q_rot;
-  float* part;
+  double2* part;
   uint16_t* o;
   float2 *a, *h1;
   uint16_t* z2;
   float2 *g, *u;
   uint16_t* act;
   float2* d;
+  size_t theta_off;   // rotary frequencies base^(-j / dc), j < dc (double)
   size_t table_off[kGroups];
   size_t table_bytes[kGroups];
 };
@@ -635,7 +733,7 @@ bool block_layout(const fairy2i_block_desc* d, BlockLayout& L) {
   L.k = take(n * 8);
   L.v = take(n * 8);
   L.q_rot = take(n * 8);
-  L.part = take(H * slices * (2 + 2 * dc) * 4);
+  L.part = take(H * slices * (2 + 2 * dc) * 8);
   L.o = take(n * 4);
   L.a = take(n * 8);
   L.h1 = take(n * 8);
@@ -661,88 +759,73 @@ void launch_attention(const BlockPlanHeader* hdr, float2* kc, float2* vc, int64_
   const int n = (int)hdr->n, H = hdr->n_heads, dc = n / H;
   const int64_t n_ctx = pos + 1;
   const int slices = (int)((n_ctx + kAttnSlice - 1) / kAttnSlice);
-  const float scale = (float)(1.0 / sqrt((double)(2 * dc)));
-  if (dc <= 64)
-    hipLaunchKernelGGL(attn_partial_kernel<1>, dim3(slices, H), dim3(kAttnThreads), 0, s, hdr->q_rot, kc, vc, dc, n_ctx,
-                       hdr->max_ctx, scale, hdr->part);
-  else
-    hipLaunchKernelGGL(attn_partial_kernel<4>, dim3(slices, H), dim3(kAttnThreads), 0, s, hdr->q_rot, kc, vc, dc, n_ctx,
-                       hdr->max_ctx, scale, hdr->part);
-  hipLaunchKernelGGL(attn_combine_kernel, dim3(H), dim3(64), 0, s, hdr->part, slices, dc, hdr->o);
+  const double scale = 1.0 / sqrt((double)(2 * dc));
+  const dim3 grid(slices, H), heads(H), block(kAttnThreads);
+  const size_t lds = sizeof(double) * (size_t)slices;
+  uint32_t* o = reinterpret_cast<uint32_t*>(hdr->o);
+  if (dc <= 64) {
+    hipLaunchKernelGGL(attn_partial_kernel<1>, grid, block, 0, s, hdr->q_rot, kc, vc, dc, n_ctx, hdr->max_ctx, scale,
+                       hdr->part);
+    hipLaunchKernelGGL(attn_combine_kernel<1>, heads, block, lds, s, hdr->part, slices, dc, o);
+  } else {
+    hipLaunchKernelGGL(attn_partial_kernel<4>, grid, block, 0, s, hdr->q_rot, kc, vc, dc, n_ctx, hdr->max_ctx, scale,
+                       hdr->part);
+    hipLaunchKernelGGL(attn_combine_kernel<4>, heads, block, lds, s, hdr->part, slices, dc, o);
+  }
 }
 
-// The fused path: the four product launches and eight block kernels.
+// The fused path: six launches.
 fairy2i_status block_decode_fused(const void* plan, const void* plan_device, const float2* xin, float2* kc,
                                   float2* vc, int64_t pos, float2* out, hipStream_t s) {
   const auto* hdr = static_cast<const BlockPlanHeader*>(plan);
-  const int n = (int)hdr->n, f = (int)hdr->n_ff, dc = n / hdr->n_heads;
-  auto gtab = [&](int gi) {
-    return reinterpret_cast<const GroupTableHeader*>(static_cast<const char*>(plan) + hdr->table_off[gi]);
-  };
-  auto layer = [&](int gi, int i) -> const DecLayer& { return reinterpret_cast<const DecLayer*>(gtab(gi) + 1)[i]; };
-  auto out_of = [&](int gi, int i) {
-    const DecLayer& l = layer(gi, i);
-    return LayerOut{l.part, l.y, l.nkc, l.N};
-  };
-  auto targets = [&](int gi) {
-    OperandTargets t{};
-    t.count = gtab(gi)->h.n_layers;
-    for (int i = 0; i < t.count; ++i) {
-      t.xf[i] = layer(gi, i).xf;
-      t.xs[i] = layer(gi, i).xs;
+  auto args = [&](int gi) {
+    const auto* gt = reinterpret_cast<const GroupTableHeader*>(static_cast<const char*>(plan) + hdr->table_off[gi]);
+    const auto* l = reinterpret_cast<const DecLayer*>(gt + 1);
+    SplitArgs a{};
+    a.K = l[0].K;
+    a.nk4 = l[0].nk4;
+    a.N = l[0].N;
+    a.code_bytes = (uint32_t)((size_t)hdr->T * (size_t)l[0].nrb * (size_t)l[0].nk4 * 1024);
+    for (int i = 0; i < gt->h.n_layers; ++i) {
+      a.m[i].codes[0] = l[i].codes[0];
+      a.m[i].codes[1] = l[i].codes[1];
+      a.m[i].scales[0] = l[i].scales[0];
+      a.m[i].scales[1] = l[i].scales[1];
+      a.m[i].y = l[i].y;
     }
-    t.nk4 = layer(gi, 0).nk4;
-    t.ctr = gtab(gi)->h.coop_ctr;
-    return t;
+    return a;
   };
-  auto product = [&](int gi) {
-    DecLayer none{};
-    const auto* td = reinterpret_cast<const DecLayer*>(static_cast<const char*>(plan_device) + hdr->table_off[gi] +
-                                                        sizeof(GroupTableHeader));
-    launch_f4_product(gtab(gi)->h, none, td, s);
-  };
-  OperandArgs a{};
-  // attention input: RMSNorm of x, operand of q, k, v
-  a.K = n;
+  SplitArgs a = args(0);
   a.x = xin;
   a.gamma = hdr->norm_attn;
   a.eps = hdr->eps;
-  a.z_out = hdr->z;
-  a.t = targets(0);
-  launch_operand<kSrcNorm>(a, s);
-  product(0);
-  hipLaunchKernelGGL(rope_append_sum_kernel, dim3((n + 255) / 256), dim3(256), 0, s, out_of(0, 0), out_of(0, 1),
-                     out_of(0, 2), n, dc, pos, hdr->max_ctx, hdr->rope_base, hdr->q_rot, kc, vc);
+  a.z_out = reinterpret_cast<uint32_t*>(hdr->z);
+  a.theta = reinterpret_cast<const double*>(static_cast<const char*>(plan_device) + hdr->theta_off);
+  a.pos = pos;
+  a.max_ctx = hdr->max_ctx;
+  a.dc = (int)(hdr->n / hdr->n_heads);
+  a.q_rot = hdr->q_rot;
+  a.k_cache = kc;
+  a.v_cache = vc;
+  launch_block_product<kSrcNorm, kOutRope>(a, hdr->T, s);
   launch_attention(hdr, kc, vc, pos, s);
-  // output projection input: the attention output as it stands
-  a = OperandArgs{};
-  a.K = n;
+  a = args(1);
   a.tok = reinterpret_cast<const uint32_t*>(hdr->o);
-  a.t = targets(1);
-  launch_operand<kSrcBf16>(a, s);
-  product(1);
-  // MLP input: h1 = x + attention branch, its RMSNorm; operand of gate and up
-  a = OperandArgs{};
-  a.K = n;
-  a.x = xin;
-  a.res = out_of(1, 0);
-  a.h_out = hdr->h1;
+  a.base = xin;
+  a.sum = hdr->h1;
+  launch_block_product<kSrcBf16, kOutAdd>(a, hdr->T, s);
+  a = args(2);
+  a.x = hdr->h1;
   a.gamma = hdr->norm_mlp;
   a.eps = hdr->eps;
-  a.z_out = hdr->z2;
-  a.t = targets(2);
-  launch_operand<kSrcNorm>(a, s);
-  product(2);
-  // down projection input: SwiGLU of gate and up
-  hipLaunchKernelGGL(swiglu_sum_kernel, dim3((f + 255) / 256), dim3(256), 0, s, out_of(2, 0), out_of(2, 1), f,
-                     reinterpret_cast<uint32_t*>(hdr->act));
-  a = OperandArgs{};
-  a.K = f;
+  a.z_out = reinterpret_cast<uint32_t*>(hdr->z2);
+  a.act = reinterpret_cast<uint32_t*>(hdr->act);
+  launch_block_product<kSrcNorm, kOutSwiglu>(a, hdr->T, s);
+  a = args(3);
   a.tok = reinterpret_cast<const uint32_t*>(hdr->act);
-  a.t = targets(3);
-  launch_operand<kSrcBf16>(a, s);
-  product(3);
-  hipLaunchKernelGGL(add_sum_kernel, dim3((n + 255) / 256), dim3(256), 0, s, hdr->h1, out_of(3, 0), n, out);
+  a.base = hdr->h1;
+  a.sum = out;
+  launch_block_product<kSrcBf16, kOutAdd>(a, hdr->T, s);
   return hip_st(hipGetLastError());
 }
 
@@ -762,7 +845,7 @@ size_t fairy2i_block_workspace_bytes(const fairy2i_block_desc* desc) {
 
 size_t fairy2i_block_plan_bytes(const fairy2i_block_desc* desc) {
   if (!block_desc_ok(desc)) return 0;
-  size_t total = align256(sizeof(BlockPlanHeader));
+  size_t total = align256(sizeof(BlockPlanHeader)) + align256(sizeof(double) * (size_t)(desc->n / desc->n_heads));
   for (int gi = 0; gi < kGroups; ++gi) total += align256(fairy2i_wl_group_table_bytes(gi == 0 ? 3 : (gi == 2 ? 2 : 1)));
   return total;
 }
@@ -798,7 +881,7 @@ fairy2i_status fairy2i_block_build_plan(const fairy2i_block_desc* desc, void* wo
   hdr->k = reinterpret_cast<float2*>(ws + L.k);
   hdr->v = reinterpret_cast<float2*>(ws + L.v);
   hdr->q_rot = reinterpret_cast<float2*>(ws + L.q_rot);
-  hdr->part = reinterpret_cast<float*>(ws + L.part);
+  hdr->part = reinterpret_cast<double2*>(ws + L.part);
   hdr->o = reinterpret_cast<uint16_t*>(ws + L.o);
   hdr->a = reinterpret_cast<float2*>(ws + L.a);
   hdr->h1 = reinterpret_cast<float2*>(ws + L.h1);
@@ -808,6 +891,11 @@ fairy2i_status fairy2i_block_build_plan(const fairy2i_block_desc* desc, void* wo
   hdr->act = reinterpret_cast<uint16_t*>(ws + L.act);
   hdr->d = reinterpret_cast<float2*>(ws + L.d);
   size_t off = align256(sizeof(BlockPlanHeader));
+  hdr->theta_off = off;
+  const int64_t dc = desc->n / desc->n_heads;
+  for (int64_t j = 0; j < dc; ++j)
+    reinterpret_cast<double*>(pl + off)[j] = pow(desc->rope_base, -2.0 * (double)j / (double)(2 * dc));
+  off += align256(sizeof(double) * (size_t)dc);
   for (int gi = 0; gi < kGroups; ++gi) {
     fairy2i_wl_layer ls[3];
     const int cnt = group_layers(desc, gi, ws, L, ls);
@@ -820,7 +908,7 @@ fairy2i_status fairy2i_block_build_plan(const fairy2i_block_desc* desc, void* wo
     hdr->table_bytes[gi] = tb;
     off += align256(tb);
   }
-  hdr->fused = desc->n <= kOpMaxK && desc->n_ff <= kOpMaxK;
+  hdr->fused = desc->n <= kSplitMaxK && desc->n_ff <= kSplitMaxK;
   for (int gi = 0; gi < kGroups; ++gi) {
     const DecHeader& h = reinterpret_cast<const GroupTableHeader*>(pl + hdr->table_off[gi])->h;
     if (h.mode != kModeBf16F4 || h.B != 1 || h.bands != 2 || h.nc != 8 || h.ntile != 1) hdr->fused = 0;
@@ -845,9 +933,7 @@ fairy2i_status fairy2i_block_decode(const void* plan, const void* plan_device, c
   if (hdr->magic != kBlockMagic || hdr->abi != (uint32_t)fairy2i_abi_version()) return FAIRY2I_ERR_UNSUPPORTED;
   if (pos < 0 || pos >= hdr->max_ctx) return FAIRY2I_ERR_SHAPE;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int n = (int)hdr->n, f = (int)hdr->n_ff, H = hdr->n_heads, dc = n / H;
-  const int64_t n_ctx = pos + 1;
-  const int slices = (int)((n_ctx + kAttnSlice - 1) / kAttnSlice);
+  const int n = (int)hdr->n, f = (int)hdr->n_ff, dc = n / hdr->n_heads;
   auto group = [&](int gi) -> fairy2i_status {
     return fairy2i_wl_matmul_group(static_cast<const char*>(plan) + hdr->table_off[gi],
                                    static_cast<const char*>(plan_device) + hdr->table_off[gi], stream);
@@ -857,7 +943,6 @@ fairy2i_status fairy2i_block_decode(const void* plan, const void* plan_device, c
   float2* vc = reinterpret_cast<float2*>(v_cache);
   hipError_t e;
   fairy2i_status st;
-  const float scale = (float)(1.0 / sqrt((double)(2 * dc)));
   if (hdr->fused) return block_decode_fused(plan, plan_device, xin, kc, vc, pos, reinterpret_cast<float2*>(out), s);
   hipLaunchKernelGGL(add_rmsnorm_kernel, dim3(1), dim3(kNormThreads), 0, s, xin, nullptr, nullptr, hdr->norm_attn,
                      hdr->eps, n, hdr->z);
@@ -865,13 +950,7 @@ fairy2i_status fairy2i_block_decode(const void* plan, const void* plan_device, c
   if ((st = group(0)) != FAIRY2I_OK) return st;
   hipLaunchKernelGGL(rope_append_kernel, dim3((n + 255) / 256), dim3(256), 0, s, hdr->q, hdr->k, hdr->v, n, dc, pos,
                      hdr->max_ctx, hdr->rope_base, hdr->q_rot, kc, vc);
-  if (dc <= 64)
-    hipLaunchKernelGGL(attn_partial_kernel<1>, dim3(slices, H), dim3(kAttnThreads), 0, s, hdr->q_rot, kc, vc, dc, n_ctx,
-                       hdr->max_ctx, scale, hdr->part);
-  else
-    hipLaunchKernelGGL(attn_partial_kernel<4>, dim3(slices, H), dim3(kAttnThreads), 0, s, hdr->q_rot, kc, vc, dc, n_ctx,
-                       hdr->max_ctx, scale, hdr->part);
-  hipLaunchKernelGGL(attn_combine_kernel, dim3(H), dim3(64), 0, s, hdr->part, slices, dc, hdr->o);
+  launch_attention(hdr, kc, vc, pos, s);
   if ((e = hipGetLastError()) != hipSuccess) return hip_st(e);
   if ((st = group(1)) != FAIRY2I_OK) return st;
   hipLaunchKernelGGL(add_rmsnorm_kernel, dim3(1), dim3(kNormThreads), 0, s, xin, hdr->a, hdr->h1, hdr->norm_mlp,

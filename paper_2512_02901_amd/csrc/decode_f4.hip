@@ -196,19 +196,6 @@ __global__ __launch_bounds__(kPrepF4Threads) void dec_prep_f4_token_kernel(DecHe
 // so the products are exact; the matrix core adds them into the float32
 // accumulators.
 
-// S and I operands of one 128-code MFMA from the lane's two code words
-// (S = I | 0x22222222: I keeps only bits 3 and 1 of each nibble).
-__device__ inline void expand_f4(uint32_t w0, uint32_t w1, v8i& bs, v8i& bi) {
-  const uint32_t ia0 = w0 & 0xAAAAAAAAu, ib0 = (w0 << 1) & 0xAAAAAAAAu;
-  const uint32_t ia1 = w1 & 0xAAAAAAAAu, ib1 = (w1 << 1) & 0xAAAAAAAAu;
-  bi = v8i{(int)ia0, (int)ib0, (int)ia1, (int)ib1, 0, 0, 0, 0};
-  bs = v8i{(int)(ia0 | 0x22222222u), (int)(ib0 | 0x22222222u), (int)(ia1 | 0x22222222u),
-           (int)(ib1 | 0x22222222u), 0, 0, 0, 0};
-}
-
-constexpr int kFmtFp8 = 0;  // MFMA operand format codes: e4m3
-constexpr int kFmtFp4 = 4;  // e2m1
-
 // Token factor tt of a tile's NF factors, selected without indexing a
 // register array by a lane-dependent value (such an array lives in scratch
 // memory, whose loads share the vector-memory queue with the code loads in

@@ -239,3 +239,32 @@ def test_block_general_path_wide_heads(gpu):
     assert err <= TOL_END
     y2 = host(blk.decode(dev(x, gpu), dev(kc, gpu), dev(vc, gpu), pos))
     np.testing.assert_array_equal(y.view(np.uint32), y2.view(np.uint32))
+
+
+@pytest.mark.parametrize("n,f,H,T,max_ctx,pos", [
+    (128, 320, 2, 1, 16, 3),           # one 256-code step or two, most waves without one
+    (192, 448, 3, 3, 70, 65),
+    (64, 64, 2, 4, 2200, 2111),        # 33 slices: a second round of the merge's loads
+    (64, 128, 2, 2, 16600, 16500),     # 258 slices: more than a merging block has threads
+    (2112, 2304, 33, 3, 130, 129),     # past 2048: several steps a wave, 16 waves, wider token strides
+    (320, 2112, 5, 4, 16, 0),          # T = 4 down projection past 2048, one cached position
+])
+def test_block_fused_edges(gpu, n, f, H, T, max_ctx, pos):
+    """The fused path at the edges of its launch rules, every stage checked."""
+    import torch
+    import paper_2512_02901_amd as f2
+    dl, cl = {}, {}
+    for i, (name, (N, K)) in enumerate(shapes(n, f).items()):
+        U, W = f2.to_widely_linear(synth.torch_llama_weight(2 * N, 2 * K, 8600 + i, gpu))
+        (cu, su), (cw, sw) = f2.quantize(U, T), f2.quantize(W, T)
+        dl[name] = (f2.repack_tiled_fp4(cu), su, f2.repack_tiled_fp4(cw), sw)
+        cl[name] = (oracle.unpack(host(cu), K), host(su), oracle.unpack(host(cw), K), host(sw))
+    x, na, nm, kc, vc = make_inputs(n, H, max_ctx, pos, 87)
+    blk = f2.WlBlock(dl, dev(na, gpu), dev(nm, gpu), n=n, n_ff=f, n_heads=H, T=T, max_ctx=max_ctx)
+    dk, dv = dev(kc, gpu), dev(vc, gpu)
+    y = host(blk.decode(dev(x, gpu), dk, dv, pos))
+    torch.cuda.synchronize()
+    flips = check_stages(blk, cl, x, na, nm, kc, host(dk), host(dv), pos, H, y)
+    print(f"n {n} f {f} T {T} pos {pos}: bf16 flips {flips}")
+    y2 = host(blk.decode(dev(x, gpu), dev(kc, gpu), dev(vc, gpu), pos))
+    np.testing.assert_array_equal(y.view(np.uint32), y2.view(np.uint32))
