@@ -379,7 +379,9 @@ fairy2i_status fairy2i_wl_matmul_group(const void* table, const void* table_devi
  * first launch, events[1] after the activation-operand kernel, events[2]
  * after the product kernel and events[3] after the split-K reduction (each
  * on `stream`, with hipEventRecord), so a caller can time each kernel of the
- * call.  events: 4 hipEvent_t created by the caller.
+ * call.  events: 4 hipEvent_t created by the caller.  A call that takes one
+ * launch (a few fp4 tiled layers, up to four tokens) records events[0] and
+ * events[1] before it and events[2] and events[3] after it.
  * Errors: as fairy2i_wl_matmul_group; FAIRY2I_ERR_NULL for NULL events.
  */
 fairy2i_status fairy2i_wl_matmul_group_timed(const void* table, const void* table_device,

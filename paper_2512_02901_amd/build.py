@@ -35,6 +35,7 @@ EXTRA = {
     # keep MFMA accumulators in VGPRs: the decode kernels accumulate across
     # steps and items, and AGPR accumulators cost copies on every step
     "decode.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "decode_f4_split.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "block.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     # and leave the cooperative kernel's one-lane claim atomics as written (the
     # atomic optimizer would read each result back at once, waiting for every

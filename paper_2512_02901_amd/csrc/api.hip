@@ -457,6 +457,7 @@ fairy2i_status fairy2i_wl_group_build_table(const fairy2i_wl_layer* layers, int3
   }
   hdr->h = h;
   hdr->any_split = any_split;
+  hdr->split = f4_split_ok(h, tab) ? 1 : 0;
   hdr->max_BN = max_BN;
   return FAIRY2I_OK;
 }
@@ -469,6 +470,17 @@ static fairy2i_status run_group(const void* table, const void* table_device, voi
     return FAIRY2I_ERR_UNSUPPORTED;
   const auto* tab_dev = reinterpret_cast<const DecLayer*>(static_cast<const char*>(table_device) +
                                                           sizeof(GroupTableHeader));
+  if (hdr->split) {
+    // one launch: it is the product of the timed call, whose other two parts are empty
+    const auto* tab = reinterpret_cast<const DecLayer*>(hdr + 1);
+    const auto* ev = reinterpret_cast<hipEvent_t const*>(events);
+    hipStream_t s = as_stream(stream);
+    hipError_t e = hipSuccess;
+    for (int i = 0; ev && e == hipSuccess && i < 2; ++i) e = hipEventRecord(ev[i], s);
+    if (e == hipSuccess) e = launch_split_f4(hdr->h, tab, s);
+    for (int i = 2; ev && e == hipSuccess && i < 4; ++i) e = hipEventRecord(ev[i], s);
+    return hip_status(e);
+  }
   DecLayer none{};
   return hip_status(launch_decode(hdr->h, none, tab_dev, hdr->any_split, hdr->max_BN, false, 0, nullptr,
                                   as_stream(stream), reinterpret_cast<hipEvent_t const*>(events)));

@@ -87,7 +87,8 @@ constexpr uint32_t kGroupMagic = 0xFA112101u;
 struct GroupTableHeader {
   uint32_t magic, abi;
   DecHeader h;
-  int32_t any_split, pad0_;
+  int32_t any_split;
+  int32_t split;  // f4_split_ok: one launch of launch_split_f4
   int64_t max_BN;
 };
 static_assert(sizeof(GroupTableHeader) % 16 == 0, "table header alignment");
@@ -117,6 +118,14 @@ size_t dec_layer_setup(DecLayer& l, const DecHeader& h, bool single, char* ws, i
 // launches of a kModeBf16F4 call (errors are left for hipGetLastError).
 void launch_f4_prep(const DecHeader& h, const DecLayer& inl, const DecLayer* tab, hipStream_t s);
 void launch_f4_product(const DecHeader& h, const DecLayer& inl, const DecLayer* tab, hipStream_t s);
+
+// One-launch product of a few layers and up to four tokens
+// (decode_f4_split.hip): whether a kModeBf16F4 call with these (host)
+// descriptors takes it, and the call.
+constexpr int kSplitLayers = 8;
+constexpr int kSplitMaxSteps = 32;  // a layer's 256-code steps: a block walks K alone
+bool f4_split_ok(const DecHeader& h, const DecLayer* tab);
+hipError_t launch_split_f4(const DecHeader& h, const DecLayer* tab, hipStream_t s);
 
 hipError_t launch_decode(const DecHeader& h, const DecLayer& inl, const DecLayer* tab,
                          int any_split, int64_t max_BN, bool export_acc, int64_t acc_elems,

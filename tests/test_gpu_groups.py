@@ -214,3 +214,41 @@ def test_grouped_stack_full_k_items(gpu):
     for B in (1, 4):
         errs, _, _ = run_grouped(layers, T, B, gpu, rng, check_layers=[0, 4, 6, 69])
         assert max(errs) <= tol_for(B, T), (B, errs)
+
+
+@pytest.mark.parametrize("T,B,G", [(1, 1, 0), (2, 1, 0), (2, 3, 0), (2, 4, 256), (3, 3, 0), (3, 4, 512), (4, 2, 256),
+                                   (4, 1, 0)])
+def test_group_fp4_one_launch_and_streaming(gpu, T, B, G):
+    """Calls of up to eight layers and four two-band tokens take the one-launch
+    kernel, a ninth layer sends the same layers through the streaming one:
+    both against the oracle, with ragged row blocks, a half-filled last tile,
+    partial and several 256-code steps a wave, unaligned tokens and (last
+    layer of the first eight) an all-zero token."""
+    import torch
+    import paper_2512_02901_amd as f2
+    from oracle import groups as og
+    shapes = [(33, 64), (16, 2048), (15, 2112), (100, 320), (7, 5504), (48, 4096), (1, 64), (17, 256), (64, 128)]
+    rng = np.random.default_rng((90, T, B, G))
+    args, refs = [], []
+    for i, (N, K) in enumerate(shapes):
+        x = synth.bf16_round_complex(synth.activations(B, K, (91, i, B)))
+        if i == 7:
+            x[B - 1] = 0
+        cu, cw = (rng.integers(0, 4, (T, N, K)).astype(np.uint8) for _ in range(2))
+        sshape = (T, N, -(-K // G), 2) if G else (T, 2)
+        su, sw = (rng.uniform(0.01, 0.02, sshape).astype(np.float32) for _ in range(2))
+        y = torch.empty((B, N), dtype=torch.complex64, device=gpu)
+        xd = bf16_dev(x, gpu)
+        if i % 3 == 1:  # two bytes past an aligned address
+            xd = torch.cat([torch.zeros(1, dtype=torch.bfloat16, device=gpu), xd.flatten()])[1:].view(B, K, 2)
+        args.append((f2.repack_tiled_fp4(dev(oracle.pack(cu), gpu)), dev(su, gpu),
+                     f2.repack_tiled_fp4(dev(oracle.pack(cw), gpu)), dev(sw, gpu), xd, None, y))
+        refs.append(og.wl_matmul_grouped(cu, su, cw, sw, x, G) if G else oracle.wl_matmul(cu, su, cw, sw, x))
+    for count in (8, 9):
+        f2.WlGroup(args[:count], T=T, B=B, layout=f2.LAYOUT_TILED_FP4, group_size=G).run()
+        torch.cuda.synchronize()
+        errs = [rel_l2(host(a[6]), r) for a, r in zip(args[:count], refs)]
+        print(f"T={T} B={B} G={G} {count} layers:", " ".join(f"{e:.2e}" for e in errs))
+        assert max(errs) <= 1e-6
+        for a in args:
+            a[6].fill_(float("nan"))
