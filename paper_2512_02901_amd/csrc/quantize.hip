@@ -25,9 +25,10 @@
 // same.  (The kernel that split every value into 32-bit limbs by shifts and
 // kept five 64-bit limbs a lane was bound by that arithmetic, 28.6 us a stage
 // of 2048 x 2048 entries, and rounding took a launch of 6.9 us more.  A T = 2
-// call took 69 us, now 37.5: per stage about 10 us for the 34 MB of entries
-// and codes at 3.4 TB/s, 4 us for the blocks' atomics and 4 us for the last
-// block's count, loads and rounding.)
+// call took 69 us, now 32: per stage 16.7 us under the profiler, of which
+// the 34 MB of entries and codes are 7 at the rate of a large copy, the
+// blocks' atomics about 4 and the last block's count, loads and rounding
+// about 4.)
 #include "common.h"
 #include "superacc.h"
 
@@ -175,12 +176,17 @@ constexpr int kTotWords = kTotCopies * kPartWords;
 // one count of all 1024 blocks made a stage 5 us longer.  64 copies of the
 // limbs in use instead of 16 changed nothing.)
 constexpr int kArrivedBit = 40, kCompleteBit = 52;
-constexpr int kQzUnroll = 4;      // bytes a thread loads before it quantises them
-constexpr int kFlushRounds = 64;  // rounds of kQzUnroll bytes (1024 values) between flushes of a lane's sums
+constexpr int kQzUnroll = 2;      // bytes a thread loads before it quantises them
+constexpr int kFlushRounds = 128;  // rounds of kQzUnroll bytes (1024 values) between flushes of a lane's sums
 
 // Stage T0 (0-based) of the per-tensor quantiser.  Grid: up to kQzMaxBlocks
-// blocks of 256, four per CU (512 blocks of 512: 41 against 37.5 us for T = 2); the loads of a round (4 x 32 bytes of entries a lane)
-// are all in flight before its arithmetic.
+// blocks of 256, four per CU (512 blocks of 512 measured a tenth slower).
+// kQzUnroll: with four bytes a round a thread took 132 registers or more, so
+// three blocks fit a CU and the grid ended in a second, nearly empty round;
+// with two it takes 100 and all 1024 are resident.  2048 x 2048, T = 2, U and
+// W with their conversion and repacking: 106.4 -> 96.1 us (four bytes capped
+// at 128 registers spill: 113; one byte and the next round's loads ahead:
+// 95.3, two bytes and those: 99.6).
 template <int T0>
 __global__ __launch_bounds__(kQzThreads) void qz_stage_kernel(const float2* __restrict__ M, int64_t nbytes,
                                                               uint8_t* __restrict__ codes,
@@ -188,40 +194,12 @@ __global__ __launch_bounds__(kQzThreads) void qz_stage_kernel(const float2* __re
                                                               unsigned long long* __restrict__ tot) {
   __shared__ unsigned long long acc[kPartWords];  // acc[2][SA_LIMBS], cnt[2]
   __shared__ bool last;
-  for (int i = threadIdx.x; i < kPartWords; i += blockDim.x) acc[i] = 0ull;
-  __syncthreads();
-
-  double s_re[T0 + 1], s_im[T0 + 1];
-  float smax = 0.0f;
-#pragma unroll
-  for (int tp = 0; tp < T0; ++tp) {
-    s_re[tp] = (double)scales[2 * tp];
-    s_im[tp] = (double)scales[2 * tp + 1];
-    smax = fmaxf(smax, fmaxf(scales[2 * tp], scales[2 * tp + 1]));
-  }
   const int lane = threadIdx.x & 63;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   const bool al16 = (reinterpret_cast<uintptr_t>(M) & 15) == 0;  // a byte's 4 entries as two 16-byte loads
-  bool placed = false;
-  FxWindow win = fx_window(1.0f);
-  FxSum sum{0, 0, 0, 0};
-  uint32_t n = 0, n1 = 0;
-  auto flush = [&]() {
-    unsigned long long v[2][2];
-    fx_totals<64>(sum, win, n, n1, v);
-    const uint32_t cn = segment_sum<64>(n), cn1 = segment_sum<64>(n1);
-    fx_to_limbs(v, win.e, acc);
-    if (lane < 2) atomicAdd(&acc[2 * SA_LIMBS + lane], (unsigned long long)(lane ? cn1 : cn - cn1));
-    sum = FxSum{0, 0, 0, 0};
-    n = n1 = 0;
-  };
-  // every lane of a wave runs the same number of rounds (the window and the
-  // flushes are the wave's); lanes past the end load nothing
-  int round = 0;
-  for (int64_t w0 = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x - lane); w0 < nbytes; w0 += kQzUnroll * stride) {
-    const int64_t b0 = w0 + lane;
-    float4 mv[kQzUnroll][2];
-    uint32_t prev[kQzUnroll][T0 + 1];
+  float4 mv[kQzUnroll][2];
+  uint32_t prev[kQzUnroll][T0 + 1];
+  auto load_round = [&](int64_t b0) {
 #pragma unroll
     for (int u = 0; u < kQzUnroll; ++u) {
       const int64_t bi = b0 + u * stride;
@@ -239,6 +217,40 @@ __global__ __launch_bounds__(kQzThreads) void qz_stage_kernel(const float2* __re
 #pragma unroll
       for (int tp = 0; tp < T0; ++tp) prev[u][tp] = ok ? codes[(int64_t)tp * nbytes + bi] : 0u;
     }
+  };
+  // the first round is asked for before anything is waited for: a matrix of
+  // up to 4 M entries has no other
+  int64_t w0 = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x - lane);
+  load_round(w0 + lane);
+  for (int i = threadIdx.x; i < kPartWords; i += blockDim.x) acc[i] = 0ull;
+  __syncthreads();
+
+  double s_re[T0 + 1], s_im[T0 + 1];
+  float smax = 0.0f;
+#pragma unroll
+  for (int tp = 0; tp < T0; ++tp) {
+    s_re[tp] = (double)scales[2 * tp];
+    s_im[tp] = (double)scales[2 * tp + 1];
+    smax = fmaxf(smax, fmaxf(scales[2 * tp], scales[2 * tp + 1]));
+  }
+  bool placed = false;
+  FxWindow win = fx_window(1.0f);
+  FxSum sum{0, 0, 0, 0};
+  uint32_t n = 0, n1 = 0;
+  auto flush = [&]() {
+    unsigned long long v[2][2];
+    fx_totals<64>(sum, win, n, n1, v);
+    const uint32_t cn = segment_sum<64>(n), cn1 = segment_sum<64>(n1);
+    fx_to_limbs(v, win.e, acc);
+    if (lane < 2) atomicAdd(&acc[2 * SA_LIMBS + lane], (unsigned long long)(lane ? cn1 : cn - cn1));
+    sum = FxSum{0, 0, 0, 0};
+    n = n1 = 0;
+  };
+  // every lane of a wave runs the same number of rounds (the window and the
+  // flushes are the wave's); lanes past the end load nothing
+  int round = 0;
+  while (w0 < nbytes) {
+    const int64_t b0 = w0 + lane;
     if (!placed) {  // the wave's first entries that are not all zero place the window
       float m = 0.0f;
 #pragma unroll
@@ -285,6 +297,8 @@ __global__ __launch_bounds__(kQzThreads) void qz_stage_kernel(const float2* __re
         codes[(int64_t)T0 * nbytes + bi] = (uint8_t)out;
       }
     }
+    w0 += kQzUnroll * stride;
+    if (w0 < nbytes) load_round(w0 + lane);
     if (++round % kFlushRounds == 0) flush();
   }
   flush();

@@ -47,6 +47,18 @@ def test_quantize_value_ranges(gpu, N, K, T, zero_rows, spread):
     np.testing.assert_array_equal(host(c), oracle.pack(codes))
 
 
+@pytest.mark.parametrize("K,T", [(1023, 1), (1024, 2), (1025, 3), (2047, 2), (2048, 4), (2049, 2)])
+def test_quantize_round_edges(gpu, K, T):
+    """256 rows of 4 K entries: one byte and two (a round) for each of the full
+    grid's 262144 threads, a row short of them and a row past."""
+    import paper_2512_02901_amd as f2
+    M = wide_matrix(256, 4 * K, 10)
+    codes, scales = oracle.quantize(M, T)
+    c, s = f2.quantize(dev(M, gpu), T)
+    np.testing.assert_array_equal(host(s).view(np.uint32), scales.view(np.uint32))
+    np.testing.assert_array_equal(host(c), oracle.pack(codes))
+
+
 def test_quantize_many_values_a_lane(gpu):
     """2^28 + 2^20 entries: a lane's sums pass through a flush.  All entries
     have the same two magnitudes, so the scales are those exactly."""
