@@ -75,12 +75,48 @@ size_t single_decode_bytes(int64_t N, int64_t K, int32_t T, int64_t B, int32_t d
 // 128 (2752) 37 / 30.
 constexpr int64_t kSplitBlocks = 1408;
 
+// The outputs lie in the memory of the activations (or their factors).
+bool outputs_over_inputs(const WlArgs& a) {
+  const auto at = [](const void* p) { return reinterpret_cast<uintptr_t>(p); };
+  const uintptr_t o = at(a.acc ? static_cast<const void*>(a.acc) : a.y);
+  const uintptr_t on = a.acc ? (uintptr_t)32 * a.T * a.B * a.N : (uintptr_t)8 * a.B * a.N;
+  const uintptr_t xn = (uintptr_t)2 * a.B * a.K * (a.dtype == FAIRY2I_ACT_I8 ? 1 : 2);
+  const auto meets = [&](const void* p, uintptr_t n) { return p && o < at(p) + n && at(p) < o + on; };
+  return meets(a.x, xn) || meets(a.x_scale, (uintptr_t)4 * a.B);
+}
+
+// The operand kernel, product and reduction of a one-layer decode call: every
+// activation is read before any output is written.
+hipError_t launch_decode_layer(const WlArgs& a, void* workspace, hipStream_t s) {
+  DecLayer l{};
+  l.codes[0] = a.codes[0];
+  l.codes[1] = a.codes[1];
+  l.scales[0] = a.scales[0];
+  l.scales[1] = a.scales[1];
+  l.x = a.x;
+  l.x_scale_in = a.x_scale;
+  l.y = a.y;
+  l.acc = a.acc;
+  l.N = (int32_t)a.N;
+  l.K = (int32_t)a.K;
+  DecHeader h = dec_header(a.T, dec_mode(a.dtype), a.B, a.acc != nullptr);
+  dec_layer_setup(l, h, true, static_cast<char*>(workspace));
+  h.n_layers = 1;
+  h.total_items = (int64_t)l.nrb * l.nkc;
+  h.total_steps = (int64_t)l.nrb * l.nk4;
+  h.max_nk4 = l.nk4;
+  return launch_decode(h, l, nullptr, l.nkc > 1, a.B * a.N, a.acc != nullptr, (int64_t)8 * a.T * a.B * a.N, a.acc, s);
+}
+
 // The product of one layer (arguments and workspace checked).
 hipError_t launch_product(const WlArgs& a, void* workspace, hipStream_t s) {
   const bool small = a.B <= FAIRY2I_MAX_DECODE_BATCH;
   if (use_mfma_decode(a.dtype, a.N, a.K, small ? a.B : 1) &&
-      (small || (a.N + 15) / 16 * ((a.B + 15) / 16) <= kSplitBlocks))
-    return launch_split(a, s);
+      (small || (a.N + 15) / 16 * ((a.B + 15) / 16) <= kSplitBlocks)) {
+    // one launch reads and writes at once
+    if (!outputs_over_inputs(a)) return launch_split(a, s);
+    if (small) return launch_decode_layer(a, workspace, s);
+  }
   return small ? launch_gemv(a, s) : launch_gemm_i8(a, workspace, s);
 }
 

@@ -256,3 +256,37 @@ def test_float_layer_not_finite(gpu, bad):
     # Re x feeds Re y through the real axis (even codes), Im y through the imaginary one
     np.testing.assert_array_equal(np.isfinite(y[1].real), odd_u & odd_w)
     np.testing.assert_array_equal(np.isfinite(y[1].imag), ~odd_u & ~odd_w)
+
+
+@pytest.mark.parametrize("dt,B", [("bf16", 1), ("bf16", 3), ("i8", 16), ("i8", 40), ("group", 1), ("group", 4)])
+def test_outputs_over_tokens(gpu, dt, B):
+    """Outputs written over the tokens' own memory: such calls read every token
+    before they write (the one-launch kernels, which do not, leave them to the
+    launches that do)."""
+    import torch
+    import paper_2512_02901_amd as f2
+    N, K, T = 512, 1024, 2
+    rng = np.random.default_rng((95, B))
+    cu, cw = (dev(rng.integers(0, 256, (T, N, K // 4)).astype(np.uint8), gpu) for _ in range(2))
+    su, sw = (dev(rng.uniform(0.01, 0.02, (T, 2)).astype(np.float32), gpu) for _ in range(2))
+    x = torch.from_numpy(rng.standard_normal((B, K, 2)).astype(np.float32)).to(gpu).to(torch.bfloat16)
+    xs = None
+    if dt == "i8":
+        x, xs = f2.quantize_act_int8(x)
+    if dt == "group":
+        cu, cw = f2.repack_tiled_fp4(cu), f2.repack_tiled_fp4(cw)
+
+    def product(tokens, y):
+        if dt == "group":
+            f2.WlGroup([(cu, su, cw, sw, tokens, None, y)], T=T, B=B, layout=f2.LAYOUT_TILED_FP4).run()
+        else:
+            f2.wl_matmul(cu, su, cw, sw, tokens, xs, out=y)
+        return host(y)
+
+    want = product(x, torch.empty((B, N), dtype=torch.complex64, device=gpu))
+    raw = torch.empty(8 * B * N, dtype=torch.uint8, device=gpu)  # as many bytes as bf16 tokens take
+    mem = raw.view(torch.complex64).view(B, N)
+    tokens = raw[:x.numel() * x.element_size()].view(x.dtype).view(x.shape)
+    tokens.copy_(x)
+    got = product(tokens, mem)
+    assert np.linalg.norm(got - want) <= 1e-6 * np.linalg.norm(want)
