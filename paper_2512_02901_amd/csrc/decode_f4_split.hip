@@ -290,9 +290,9 @@ void launch_split_f4_t(const SplitGroup& a, bool gs, unsigned blocks, hipStream_
 
 // Every block encodes its tokens itself, so the one launch costs more per row
 // block than the streaming product, against the two launches it saves.  It is
-// taken while the call's row blocks are at most this many per CU: 4 for one or
-// two tokens and 3 for three or four, 2 at T >= 3 (whose blocks have a CU to
-// themselves).  One launch / streaming, us ("all seven" layers of a decoder
+// taken while the call's row blocks are at most this many per CU: 4 at T = 1
+// and for one or two tokens at T = 2, 3 for three or four, 2 at T >= 3 (whose
+// blocks have a CU to themselves).  One launch / streaming, us ("all seven" layers of a decoder
 // block):
 //   n = 2048, n_ff = 5504, T = 2
 //     q k v        384 row blocks   1 token  7.4 / 14.3, 2  8.4 / 14.9, 4 12.0 / 18.7
@@ -302,6 +302,7 @@ void launch_split_f4_t(const SplitGroup& a, bool gs, unsigned blocks, hipStream_
 //     all seven   1328              1 token 22.1 / 21.9, 2 25.5 / 23.9, 4 43.4 / 30.7
 //   n = 512, T = 2, all seven: n_ff = 5504, 848: 1 token 13.4 / 18.6, 4 22.3 / 22.1
 //                              n_ff = 8192, 1184: 1 token 18.1 / 22.6, 4 31.9 / 29.0
+//   n = 1024, n_ff = 5504, T = 1, all seven, 1008: 4 tokens 19.6 / 23.5
 //   n = 2048, T = 3, q k v, 384: 4 tokens 16.7 / 19.8; T = 4: 1 token 12.8 / 16.7
 //   n_ff = 5504, gate, up, 688: n = 1536, T = 3, 2 tokens 19.2 / 17.6;
 //                               n = 1024, T = 4, 2 tokens 17.7 / 16.7
@@ -322,7 +323,7 @@ bool f4_split_ok(const DecHeader& h, const DecLayer* tab) {
       if (y0 < x1 && x0 < y1) return false;
     }
   }
-  return blocks <= kSplitBlocksUnit * (h.T >= 3 ? 2 : h.B > 2 ? 3 : 4);
+  return blocks <= kSplitBlocksUnit * (h.T >= 3 ? 2 : h.T == 2 && h.B > 2 ? 3 : 4);
 }
 
 hipError_t launch_split_f4(const DecHeader& h, const DecLayer* tab, hipStream_t s) {
