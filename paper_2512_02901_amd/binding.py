@@ -139,10 +139,10 @@ def _torch():
     global _torch_module, _raw_stream
     if _torch_module is None:
         import torch
-        _torch_module = torch
         # the handle alone (0.07 us); torch.cuda.current_stream builds a Stream object for it (1.9 us)
         _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or \
             (lambda index: torch.cuda.current_stream(index).cuda_stream)
+        _torch_module = torch  # last: another thread that sees the module calls _raw_stream
     return _torch_module
 
 

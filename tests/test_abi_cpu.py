@@ -342,3 +342,25 @@ def test_realify_codes_validation(lib):
     assert rc(P, P, P, P, 2, 4, 6, P, None) == binding.ERR_SHAPE        # K % 4
     assert rc(P, P, P, P, 2, 0, 8, P, None) == binding.ERR_SHAPE
     assert rc(P, P, P, P, 2, 4, 8, ctypes.c_void_p(0x1008), None) == binding.ERR_SHAPE   # R not 16-byte aligned
+
+
+def test_module_published_after_the_stream_lookup(monkeypatch):
+    """A thread that finds binding._torch_module set calls binding._raw_stream
+    without a further check, so the module may be published last only."""
+    import sys
+    import types
+
+    class Torch(types.ModuleType):
+        seen = None
+
+        @property
+        def _C(self):  # read while _torch() looks the stream function up
+            Torch.seen = (binding._torch_module, binding._raw_stream)
+            return types.SimpleNamespace(_cuda_getCurrentRawStream=lambda index: index)
+
+    monkeypatch.setitem(sys.modules, "torch", Torch("torch"))
+    monkeypatch.setattr(binding, "_torch_module", None)
+    monkeypatch.setattr(binding, "_raw_stream", None)
+    assert binding._torch() is sys.modules["torch"]
+    assert Torch.seen == (None, None)
+    assert binding._raw_stream(3) == 3
