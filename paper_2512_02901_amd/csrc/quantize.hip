@@ -313,10 +313,10 @@ __global__ __launch_bounds__(kQzThreads) void qz_stage_kernel(const float2* __re
       if (acc[i]) atomicAdd(&tc[i], acc[i]);
     // The totals are touched by device-scope atomics only, which are performed
     // at the device's point of coherence: once this block's have been performed
-    // (the wait), the counts of arrived blocks and complete copies tell the
-    // last one that all have.  A release fence would write back the codes in
-    // the L2 for each block.
-    __builtin_amdgcn_s_waitcnt(0);
+    // (the wait, which the compiler may move no memory access across), the
+    // counts of arrived blocks and complete copies tell the last one that all
+    // have.  A release fence would write back the codes in the L2 for each block.
+    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0) {
       const unsigned in_copy = (gridDim.x - copy + kTotCopies - 1) / kTotCopies;  // blocks of this copy

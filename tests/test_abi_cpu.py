@@ -364,3 +364,29 @@ def test_module_published_after_the_stream_lookup(monkeypatch):
     assert binding._torch() is sys.modules["torch"]
     assert Torch.seen == (None, None)
     assert binding._raw_stream(3) == 3
+
+
+def test_quantiser_totals_ordered_before_the_arrival_count(tmp_path):
+    """Each per-tensor stage kernel adds its words to the totals, waits for
+    those additions, and only then counts its block as arrived.  The totals are
+    relaxed atomics, so the wait itself has to keep the compiler from moving
+    them below the count: it is an asm with a memory clobber, and in the device
+    code it stands between the additions (no result) and the counts (one each
+    of the block's copy and of the copies)."""
+    import subprocess
+    from paper_2512_02901_amd import build
+    src = os.path.join(build.CSRC, "quantize.hip")
+    assert open(src).read().count('__asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");') == 1
+    out = tmp_path / "quantize.s"
+    flags = [f for f in build.CXXFLAGS if f != "-fPIC"]
+    subprocess.run([build.HIPCC, *flags, "--offload-device-only", "-S", src, "-o", str(out)], check=True,
+                   capture_output=True)
+    kernels = re.findall(r"^_ZN\S*qz_stage_kernel\S*:(.*?)^\s*s_endpgm", out.read_text(), flags=re.M | re.S)
+    assert len(kernels) == 4
+    for body in kernels:
+        lines = [l.strip() for l in body.splitlines() if l.strip()]
+        wait, = [i for i, l in enumerate(lines) if l.startswith("s_waitcnt vmcnt(0)") and "ASMSTART" in lines[i - 1]]
+        atomics = [i for i, l in enumerate(lines) if l.startswith("global_atomic_add")]
+        adds, counts = ([i for i in atomics if ("sc0" in lines[i]) == r] for r in (False, True))
+        assert adds and len(counts) == 2 and max(adds) < wait < min(counts)
+        assert any(l.startswith("s_barrier") for l in lines[wait:min(counts)])
