@@ -146,6 +146,15 @@ __device__ inline void limbs_add(unsigned long long* acc, double v) {
   if (hi) atomicAdd(&acc[limb + 2], (unsigned long long)hi);
 }
 
+// What the wave's lanes wrote to LDS before is what they read after: LDS serves
+// a wave in order, the fences keep the compiler's order (a lane that adds
+// nothing could otherwise keep the zero it stored).
+__device__ inline void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // The residual of one entry after a stage whose code for it is k.
 __device__ inline void subtract_stage(double& re, double& im, uint32_t k, double s_re, double s_im) {
   const double s = (k & 1u) ? s_im : s_re;
@@ -456,8 +465,7 @@ __global__ __launch_bounds__(kQzgThreads) void qzg_kernel(const float2* __restri
       const int ts = __builtin_ctzll(todo) / LPG;
       unsigned long long* acc = &limbs[wave][0][0];
       for (int i = lane; i < 2 * SA_LIMBS; i += 64) acc[i] = 0ull;
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_s_waitcnt(0);
+      wave_sync();
       if (seg == ts) {
 #pragma unroll
         for (int u = 0; u < NB; ++u)
@@ -469,8 +477,7 @@ __global__ __launch_bounds__(kQzgThreads) void qzg_kernel(const float2* __restri
             }
           }
       }
-      __builtin_amdgcn_s_waitcnt(0);
-      __builtin_amdgcn_wave_barrier();
+      wave_sync();
 #pragma unroll
       for (int axis = 0; axis < 2; ++axis) {
         int lo, hi;
@@ -478,8 +485,7 @@ __global__ __launch_bounds__(kQzgThreads) void qzg_kernel(const float2* __restri
         const uint32_t c = axis ? odds : evens;
         if (seg == ts) s[axis] = c ? sa_mean_range(reinterpret_cast<const uint64_t*>(acc) + axis * SA_LIMBS, lo, hi, c) : 0.0f;
       }
-      __builtin_amdgcn_s_waitcnt(0);
-      __builtin_amdgcn_wave_barrier();
+      wave_sync();
       const unsigned long long mask = LPG == 64 ? ~0ull : ((1ull << (LPG % 64)) - 1) << (ts * LPG % 64);
       todo &= ~mask;
     }
