@@ -196,11 +196,14 @@ def test_bf16_layer_edges(gpu, N, K, B, T):
         assert not y[B // 2].any()
 
 
-@pytest.mark.parametrize("B,K,off", [(1, 4, 0), (3, 2048, 0), (2, 8192, 0), (2, 8196, 0), (5, 1500, 1), (2, 6, 0)])
+@pytest.mark.parametrize("B,K,off", [(1, 4, 0), (3, 2048, 0), (2, 8192, 0), (2, 8196, 0), (5, 1500, 1), (2, 6, 0),
+                                     (3, 252, 0), (2, 256, 0), (3, 260, 0), (2, 512, 0), (3, 516, 0), (2, 1024, 0),
+                                     (3, 1028, 0)])
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 def test_act_quant_edges(gpu, B, K, off, dt):
-    """Around the eight-value groups and the most that a thread block keeps in
-    registers; misaligned tokens and odd widths go one value at a time."""
+    """Around the eight-value groups, the widths of the thread blocks and the
+    most that one keeps in registers; misaligned tokens and odd widths go one
+    value at a time."""
     import torch
     import paper_2512_02901_amd as f2
     rng = np.random.default_rng(K)
