@@ -63,7 +63,7 @@ __global__ __launch_bounds__(256) void act_quant_kernel(const void* __restrict__
 // most of them idle, many tokens were slower than one value at a time (bf16,
 // one value at a time / 512 threads / now: 4096 tokens of K = 256 6.5 / 10.1 /
 // 3.8 us, K = 512 8.3 / 10.6 / 4.5, K = 1024 11.1 / 11.6 / 6.9; 100,000 of
-// K = 64 69 / 178 / 19; from K = 2048 on 512 threads are right: 22.7 / 14.2).
+// K = 64 69 / 178 / 25; from K = 2048 on 512 threads are right: 22.7 / 14.2).
 template <int DT, int NT, int GROUPS>
 __global__ __launch_bounds__(NT) void act_quant_vec_kernel(const void* __restrict__ x, int groups,
                                                            uint2* __restrict__ q, float* __restrict__ x_scale) {
