@@ -78,8 +78,7 @@ constexpr int64_t kSplitBlocks = 1408;
 // The outputs lie in the memory of the activations (or their factors).
 bool outputs_over_inputs(const WlArgs& a) {
   const auto at = [](const void* p) { return reinterpret_cast<uintptr_t>(p); };
-  const uintptr_t o = at(a.acc ? static_cast<const void*>(a.acc) : a.y);
-  const uintptr_t on = a.acc ? (uintptr_t)32 * a.T * a.B * a.N : (uintptr_t)8 * a.B * a.N;
+  const uintptr_t o = at(a.y), on = (uintptr_t)8 * a.B * a.N;
   const uintptr_t xn = (uintptr_t)2 * a.B * a.K * (a.dtype == FAIRY2I_ACT_I8 ? 1 : 2);
   const auto meets = [&](const void* p, uintptr_t n) { return p && o < at(p) + n && at(p) < o + on; };
   return meets(a.x, xn) || meets(a.x_scale, (uintptr_t)4 * a.B);
@@ -111,10 +110,14 @@ hipError_t launch_decode_layer(const WlArgs& a, void* workspace, hipStream_t s) 
 // The product of one layer (arguments and workspace checked).
 hipError_t launch_product(const WlArgs& a, void* workspace, hipStream_t s) {
   const bool small = a.B <= FAIRY2I_MAX_DECODE_BATCH;
-  if (use_mfma_decode(a.dtype, a.N, a.K, small ? a.B : 1) &&
-      (small || (a.N + 15) / 16 * ((a.B + 15) / 16) <= kSplitBlocks)) {
+  if (use_mfma_decode(a.dtype, a.N, a.K, small ? a.B : 1)) {
+    // The accumulator export stays with the launches that store every sum
+    // once: in the one launch a wave holds a share of each, and clearing acc
+    // and adding the shares to it took 163 us against 26 (2048 x 2048, T = 2,
+    // 64 tokens), 49 against 22 (16 tokens).
+    const bool split = !a.acc && (small || (a.N + 15) / 16 * ((a.B + 15) / 16) <= kSplitBlocks);
     // one launch reads and writes at once
-    if (!outputs_over_inputs(a)) return launch_split(a, s);
+    if (split && !outputs_over_inputs(a)) return launch_split(a, s);
     if (small) return launch_decode_layer(a, workspace, s);
   }
   return small ? launch_gemv(a, s) : launch_gemm_i8(a, workspace, s);

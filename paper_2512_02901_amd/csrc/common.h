@@ -48,7 +48,7 @@ struct WlArgs {
 
 hipError_t launch_gemv(const WlArgs& a, hipStream_t stream);       // B <= 16
 // bf16 (B <= 16) and int8 activations, K % 64 == 0, code planes below 2^31
-// bytes: one launch, no workspace (the accumulator export clears acc first).
+// bytes: one launch, no workspace; y only (no accumulator export).
 hipError_t launch_split(const WlArgs& a, hipStream_t stream);
 // int8, any B.  With a workspace of gemm_workspace_bytes (> 0 only when
 // K % 64 == 0 and sizes fit 32-bit offsets) the pipelined kernel runs, else

@@ -100,7 +100,7 @@ struct CodeLoader {
 // together lie in different banks.
 constexpr int kXBytes = 16 * 512;
 
-template <int T, int kWaves, bool EXPORT>
+template <int T, int kWaves>
 __global__ __launch_bounds__(64 * kWaves, T <= 3 || kWaves > 4 ? 2 : 1) void split_i8_kernel(WlArgs a, bool vec) {
 #if defined(__HIP_DEVICE_COMPILE__)  // buffer-descriptor and LDS-DMA code: device pass only
   constexpr int P = 2 * T;
@@ -192,59 +192,40 @@ __global__ __launch_bounds__(64 * kWaves, T <= 3 || kWaves > 4 ? 2 : 1) void spl
     b ^= 1;
   }
 
-  if constexpr (EXPORT) {
-    // integer sums: the waves' shares in any order (acc was cleared before)
-    const int64_t tok = tok0 + li;
-    if (wave >= steps || tok >= a.B) return;
+  // 17: the sums below read a token's rows, the stores here a row's tokens
+  auto* part = reinterpret_cast<double2(*)[16][17]>(lds);
+  float sc[2][T][2];
+  sload_scales<T>(a.scales[0], a.scales[1], sc);
+  __syncthreads();  // every wave is done with its activations
+  if (wave < steps) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int64_t row = row0 + 4 * g + r;
-      if (row >= a.N) continue;
-#pragma unroll
-      for (int p = 0; p < P; ++p)
-#pragma unroll
-        for (int ax = 0; ax < 2; ++ax) {
-          int32_t* dst = a.acc + ((((int64_t)p * 2 + ax) * a.B + tok) * a.N + row) * 2;
-          atomicAdd(dst, acc[p][ax][0][r]);
-          atomicAdd(dst + 1, acc[p][ax][1][r]);
-        }
-    }
-  } else {
-    // 17: the sums below read a token's rows, the stores here a row's tokens
-    auto* part = reinterpret_cast<double2(*)[16][17]>(lds);
-    float sc[2][T][2];
-    sload_scales<T>(a.scales[0], a.scales[1], sc);
-    __syncthreads();  // every wave is done with its activations
-    if (wave < steps) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        double yr = 0.0, yi = 0.0;
-#pragma unroll
-        for (int t = 0; t < T; ++t) {
-          const double su_re = sc[0][t][0], su_im = sc[0][t][1], sw_re = sc[1][t][0], sw_im = sc[1][t][1];
-          const int pu = t, pw = T + t;
-          yr += su_re * (double)acc[pu][0][0][r] - su_im * (double)acc[pu][1][1][r];
-          yi += su_re * (double)acc[pu][0][1][r] + su_im * (double)acc[pu][1][0][r];
-          yr += sw_re * (double)acc[pw][0][0][r] + sw_im * (double)acc[pw][1][1][r];
-          yi += -sw_re * (double)acc[pw][0][1][r] + sw_im * (double)acc[pw][1][0][r];
-        }
-        part[wave][li][4 * g + r] = make_double2(yr, yi);
-      }
-    }
-    __syncthreads();
-    const int active = steps < kWaves ? steps : kWaves;
-    for (int o = threadIdx.x; o < 256; o += 64 * kWaves) {
-      const int t = o >> 4, r = o & 15;
-      const int64_t tok = tok0 + t, row = row0 + r;
-      if (tok >= a.B || row >= a.N) continue;
       double yr = 0.0, yi = 0.0;
-      for (int w = 0; w < active; ++w) {
-        yr += part[w][t][r].x;
-        yi += part[w][t][r].y;
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        const double su_re = sc[0][t][0], su_im = sc[0][t][1], sw_re = sc[1][t][0], sw_im = sc[1][t][1];
+        const int pu = t, pw = T + t;
+        yr += su_re * (double)acc[pu][0][0][r] - su_im * (double)acc[pu][1][1][r];
+        yi += su_re * (double)acc[pu][0][1][r] + su_im * (double)acc[pu][1][0][r];
+        yr += sw_re * (double)acc[pw][0][0][r] + sw_im * (double)acc[pw][1][1][r];
+        yi += -sw_re * (double)acc[pw][0][1][r] + sw_im * (double)acc[pw][1][0][r];
       }
-      const double s = (double)a.x_scale[tok];
-      a.y[tok * a.N + row] = make_float2((float)(yr * s), (float)(yi * s));
+      part[wave][li][4 * g + r] = make_double2(yr, yi);
     }
+  }
+  __syncthreads();
+  const int active = steps < kWaves ? steps : kWaves;
+  for (int o = threadIdx.x; o < 256; o += 64 * kWaves) {
+    const int t = o >> 4, r = o & 15;
+    const int64_t tok = tok0 + t, row = row0 + r;
+    if (tok >= a.B || row >= a.N) continue;
+    double yr = 0.0, yi = 0.0;
+    for (int w = 0; w < active; ++w) {
+      yr += part[w][t][r].x;
+      yi += part[w][t][r].y;
+    }
+    const double s = (double)a.x_scale[tok];
+    a.y[tok * a.N + row] = make_float2((float)(yr * s), (float)(yi * s));
   }
 #endif
 }
@@ -410,10 +391,6 @@ __global__ __launch_bounds__(64 * kWaves) void split_bf16_kernel(WlArgs a, bool 
 #endif
 }
 
-__global__ void clear_i32_kernel(int32_t* p, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = 0;
-}
-
 // Waves per block: four (two blocks on a CU hide each other's waits), eight
 // where K is long and the blocks are too few for that.  2048 x 5504, T = 2,
 // four against eight waves: int8 16 tokens (128 blocks) 11.3 / 10.6 us, 77
@@ -422,17 +399,17 @@ __global__ void clear_i32_kernel(int32_t* p, int64_t n) {
 // (T = 4 int8 accumulators leave eight waves too few registers.)
 bool eight_waves(const WlArgs& a, int64_t blocks, int64_t most) { return a.K > 2048 && blocks <= most; }
 
-template <int T, bool EXPORT>
+template <int T>
 void launch_i8(const WlArgs& a, hipStream_t s) {
   const bool vec = (reinterpret_cast<uintptr_t>(a.x) & 15) == 0;
   const dim3 grid((unsigned)((a.N + 15) / 16), (unsigned)((a.B + 15) / 16));
   if constexpr (T <= 3) {
     if (eight_waves(a, (int64_t)grid.x * grid.y, 256)) {
-      hipLaunchKernelGGL((split_i8_kernel<T, 8, EXPORT>), grid, dim3(512), 0, s, a, vec);
+      hipLaunchKernelGGL((split_i8_kernel<T, 8>), grid, dim3(512), 0, s, a, vec);
       return;
     }
   }
-  hipLaunchKernelGGL((split_i8_kernel<T, 4, EXPORT>), grid, dim3(256), 0, s, a, vec);
+  hipLaunchKernelGGL((split_i8_kernel<T, 4>), grid, dim3(256), 0, s, a, vec);
 }
 
 template <int T>
@@ -448,22 +425,12 @@ void launch_bf16(const WlArgs& a, hipStream_t s) {
 }  // namespace
 
 hipError_t launch_split(const WlArgs& a, hipStream_t s) {
-  if (a.acc) {
-    hipLaunchKernelGGL(clear_i32_kernel, dim3(1024), dim3(256), 0, s, a.acc, (int64_t)8 * a.T * a.B * a.N);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+  if (a.dtype == FAIRY2I_ACT_I8) {
     switch (a.T) {
-      case 1: launch_i8<1, true>(a, s); break;
-      case 2: launch_i8<2, true>(a, s); break;
-      case 3: launch_i8<3, true>(a, s); break;
-      default: launch_i8<4, true>(a, s); break;
-    }
-  } else if (a.dtype == FAIRY2I_ACT_I8) {
-    switch (a.T) {
-      case 1: launch_i8<1, false>(a, s); break;
-      case 2: launch_i8<2, false>(a, s); break;
-      case 3: launch_i8<3, false>(a, s); break;
-      default: launch_i8<4, false>(a, s); break;
+      case 1: launch_i8<1>(a, s); break;
+      case 2: launch_i8<2>(a, s); break;
+      case 3: launch_i8<3>(a, s); break;
+      default: launch_i8<4>(a, s); break;
     }
   } else {
     switch (a.T) {
