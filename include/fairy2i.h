@@ -186,12 +186,12 @@ size_t fairy2i_wl_matmul_workspace_bytes(int64_t N, int64_t K, int32_t T, int64_
  * B <= FAIRY2I_MAX_DECODE_BATCH: bf16 and int8 activations with
  * K % 64 == 0 go to the int8 matrix cores (bf16 tokens as a 23-bit block
  * fixed point, exact for every value within 2^14 of the token's largest
- * magnitude, smaller values rounded to that grid) in one launch, other
- * cases to a float32 / int32 vector kernel.  Larger B needs FAIRY2I_ACT_I8;
- * with K % 64 == 0 a few dozen to a few hundred tokens (the fewer the larger
- * N) take the same one-launch kernel, more run the int8-MFMA prefill GEMM
- * (sizes within 32-bit offsets): a workspace holds the activations in the
- * matrix-core operand layout and the GEMM streams operands through LDS.
+ * magnitude, smaller values rounded to that grid), other cases to a float32 /
+ * int32 vector kernel.  Larger B needs FAIRY2I_ACT_I8; with K % 64 == 0 it
+ * runs the int8-MFMA prefill GEMM (sizes within 32-bit offsets): a workspace
+ * holds the activations in the matrix-core operand layout and the GEMM streams
+ * operands through LDS.  With K % 64 == 0 calls of few rows and tokens take
+ * one launch instead, without the workspace.
  * Any other K runs a direct kernel without workspace.
  * workspace: at least fairy2i_wl_matmul_workspace_bytes(...) bytes of
  * device memory (may be NULL when that is 0), contents ignored on entry.

@@ -67,13 +67,75 @@ size_t single_decode_bytes(int64_t N, int64_t K, int32_t T, int64_t B, int32_t d
   return best;
 }
 
-// The split kernel's time grows with its blocks (16 rows x 16 tokens each),
-// the prefill GEMM's hardly at all while its own (32 x 64) do not fill the
-// GPU: they cross near this many.  T = 2, split / prefill, us: 2048 x 5504,
-// 128 tokens (1024 blocks) 31 / 46, 256 (2048) 58 / 50; 2048 x 2048, 128
-// tokens 15.8 / 20.9, 256 28.5 / 22.7; 5504 x 2048, 64 tokens (1376) 21 / 28,
-// 128 (2752) 37 / 30.
-constexpr int64_t kSplitBlocks = 1408;
+// Whether the one-launch product of a layer (K % 64 == 0) beats the launches
+// that it replaces.  Its blocks own 16 rows and 16 int8 or two bf16 tokens and
+// walk K alone, so it loses where the other side streams the codes once for
+// all tokens over many rows, and where K is so long that a wave's chain of
+// steps costs more than the slices of K and their reduction.  The lines are
+// where the two sides, timed over N 16 .. 128256, K 64 .. 262144, T 1 .. 4,
+// cross; one launch / the others, us, on either side of each:
+bool one_launch_pays(const WlArgs& a) {
+  const int64_t rb = (a.N + 15) / 16, steps = (a.K + 255) / 256, B = a.B, K = a.K;
+  const int32_t T = a.T;
+  if (B > FAIRY2I_MAX_DECODE_BATCH) {
+    // Against the prefill GEMM, whose time hardly grows while its own blocks
+    // (32 x 64) do not fill the GPU, but which walks K in one block: the
+    // shorter K, the fewer blocks pay.  T = 2, K = 5504: 1024 blocks 31 / 47,
+    // 1408 46 / 48; 2048: 1024 15 / 21, 1376 21.9 / 22.3; 512: 1024 9.4 / 10.9,
+    // 1152 11.8 / 11.1; 64: 512 5.5 / 6.6, 688 7.0 / 6.4; T = 3, 320: 768 9.5 /
+    // 10.3, 1024 11.3 / 10.3.  T = 4 takes a CU a block of four waves: 5504:
+    // 1024 76 / 77; 2048: 768 26 / 33, 1024 34 / 33; 512: 512 11 / 14, 688
+    // 15 / 13; 64: 256 6.6 / 9.2, 512 11.6 / 9.2.
+    const int64_t most = T == 4      ? K >= 3072 ? 1024 : K >= 1024 ? 768 : K >= 256 ? 512 : 256
+                         : K >= 2048 ? 1408
+                         : K >= 1024 ? 1280
+                         : K >= 512  ? 1024
+                         : K >= 256  ? (T == 3 ? 768 : 1024)
+                                     : (T == 1 ? 1024 : 512);
+    return rb * ((B + 15) / 16) <= most;
+  }
+  if (a.dtype == FAIRY2I_ACT_BF16) {
+    // Long K, one token: 512 x 65536 T = 2 86 / 66, 1024 x 32768 54 / 46, but
+    // 256 x 32768 43 / 51; two: 512 x 65536 T = 1 72 / 92, 1024 x 32768 T = 3
+    // 66 / 69, T = 4 77 / 73; more: 512 x 65536, 4, T = 4 133 / 162, 16 x 262144
+    // 523 / 395.
+    if (steps > 64) return (T <= 2 && rb <= 16) || (B > (T == 1 ? 1 : 2) && steps <= 256) || (B == 2 && T < 4 && steps <= 128);
+    // Many rows: a block takes two tokens, so blocks = row blocks x pairs.
+    // T = 1 24000 x 4096 16 tokens (12000) 155 / 141, 12 (9000) 118 / 129, one
+    // token 32000 rows 30.3 / 29.2; T = 2 11008 x 4096 16 (5504) 105 / 98,
+    // 24000 x 2048 6 (4500) 55 / 64, 12 (9000) 79 / 79; T = 3 24000 x 4096 8
+    // (6000) 163 / 166, 16000 x 2048 16 (8000) 125 / 121; T = 4 5504 x 5504 16
+    // (2752) 135 / 149, 24000 x 4096 4 (3000) 118 / 115, 6 (4500) 169 / 196 (the
+    // other side's cost for 5, 6 and 9 .. 12 tokens is that of 8 and 16); one token of 128256 x
+    // 2048 T = 2 113 / 101.
+    const int64_t most = T == 1 ? 9000 : T == 2 ? (B > 8 && B <= 12 ? 9000 : 4500)
+                         : T == 3 ? 6000 : (B > 4 && B <= 6 ? 4500 : 2800);
+    return rb <= (T == 1 || (T == 2 && B > 2) ? 1536 : 2048) && rb * ((B + 1) / 2) <= most;
+  }
+  // int8: one block of rows serves 16 tokens, the other side's operand eight.
+  if (T == 4) {  // four waves a block, a block a CU
+    // 4096 x 4096, 256 blocks, B <= 8, 15 / 17; 5504 x 2048, 344, 17.3 / 15.6, but
+    // 8000 x 2048, two nearly full rounds, 18.3 / 20.2; 2048 x 5504, one token
+    // 23.5 / 21.8 (cold), 4 tokens 20 / 23; 4096 x 11008 4 36 / 41; 2048 x 16384 4
+    // 47 / 35; 128 x 8192 25 / 18.  16 tokens: 5504 x 5504 40 / 61, 1024 x 32768 82 / 87, 64 x 16384
+    // 42 / 31, 512 x 65536 155 / 122, 64000 x 512 67 / 46.
+    if (B <= 8) return rb <= 256 ? steps <= (B <= 2 ? 16 : rb > 128 ? 48 : 22) : rb > 448 && rb <= 512 && steps <= 8;
+    return (steps <= 32 || (rb >= 64 && steps <= 128)) && rb <= 2048;
+  }
+  // Long K: T = 1 512 x 65536 1 token 46 / 32, 16 47 / 79, 1024 x 32768 4 tokens
+  // 26 / 29; T = 2 1024 x 32768 4 37 / 35, 256 x 32768 1 36 / 41; 16 x 262144
+  // T = 1 166 / 236, T = 2 251 / 229; T = 3 2048 x 16384 1 29 / 25, 256 x 32768
+  // 8 48 / 58, 1024 x 32768 8 51 / 45, 12 51 / 79.
+  if (T == 3 && steps >= 64) return steps <= 512 && (B > 8 || (B > 4 && rb <= 16));
+  if (T == 2 && steps > 64) return steps <= 512 && (B > 4 || rb <= 16);
+  if (T == 1 && steps > 64) return B > 4 || rb <= 16 || (B > 2 && steps <= 128);
+  // Many rows: 24000 x 4096 T = 1 1 token 22.9 / 21.1, 24000 x 2048 8 15.6 / 19.5,
+  // 32000 x 4096 16 32 / 56; T = 2 32000 x 4096 1 42.5 / 42, 128256 x 2048 8
+  // 99 / 89; T = 3 24000 x 2048 1 27.1 / 25.2, 8 28 / 32, 24000 x 4096 1 45 / 46;
+  // 64000 x 512 T = 1 16 25 / 18, T = 2 16 31 / 32.
+  if (B > 8) return T > 1 || steps > 2 || rb <= 1024;
+  return rb <= (T == 2 || (T == 3 && (steps >= 16 || B >= 4)) ? 2048 : T == 1 && B > 4 ? 1536 : 1024);
+}
 
 // The outputs lie in the memory of the activations (or their factors).
 bool outputs_over_inputs(const WlArgs& a) {
@@ -115,9 +177,8 @@ hipError_t launch_product(const WlArgs& a, void* workspace, hipStream_t s) {
     // once: in the one launch a wave holds a share of each, and clearing acc
     // and adding the shares to it took 163 us against 26 (2048 x 2048, T = 2,
     // 64 tokens), 49 against 22 (16 tokens).
-    const bool split = !a.acc && (small || (a.N + 15) / 16 * ((a.B + 15) / 16) <= kSplitBlocks);
-    // one launch reads and writes at once
-    if (split && !outputs_over_inputs(a)) return launch_split(a, s);
+    // One launch also reads and writes at once.
+    if (!a.acc && one_launch_pays(a) && !outputs_over_inputs(a)) return launch_split(a, s);
     if (small) return launch_decode_layer(a, workspace, s);
   }
   return small ? launch_gemv(a, s) : launch_gemm_i8(a, workspace, s);

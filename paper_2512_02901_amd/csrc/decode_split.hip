@@ -23,6 +23,8 @@
 //   2048 x 5504   bf16 1 token 22.3 -> 11.0, 16 tokens 49.5 -> 30.2;
 //                 int8 1 token 17.9 -> 10.5, 16 tokens 32.0 -> 10.7, 80 45.0 -> 24.3
 //   5504 x 5504   int8 16 tokens 39.7 -> 17.3, 64 tokens 46.1 -> 44.4
+// Many rows, long K and (T = 4) int8 layers of more blocks than CUs stay with
+// the other kernels: one_launch_pays (api.hip).
 //
 // Products and recombination are those of the grouped int8 path: each code
 // word of 16 codes expands in registers into the b_re and b_im int8 planes,

@@ -196,6 +196,35 @@ def test_bf16_layer_edges(gpu, N, K, B, T):
         assert not y[B // 2].any()
 
 
+# either side of the lines between the one launch and the launches that it
+# replaces: many rows, long K, tokens against the prefill GEMM
+
+@pytest.mark.parametrize("dt,T,N,K,B", [
+    ("bf16", 1, 24576, 64, 1), ("bf16", 1, 24592, 64, 1), ("bf16", 4, 5600, 64, 16), ("bf16", 4, 5616, 64, 16),
+    ("bf16", 2, 16, 16384, 1), ("bf16", 2, 272, 16448, 1), ("bf16", 3, 32, 33024, 2), ("bf16", 2, 30, 32768, 2),
+    ("i8", 1, 16384, 64, 3), ("i8", 1, 16400, 64, 3), ("i8", 4, 33, 5504, 4), ("i8", 4, 33, 5696, 4),
+    ("i8", 4, 4112, 64, 2), ("i8", 4, 32, 8256, 16), ("i8", 3, 17, 16128, 1), ("i8", 3, 17, 16384, 1),
+    ("i8", 2, 272, 16640, 4), ("i8", 2, 16, 16640, 4), ("i8", 3, 16384, 64, 32), ("i8", 2, 8192, 64, 17),
+    ("i8", 4, 4096, 256, 33), ("i8", 2, 7680, 320, 48), ("i8", 3, 7680, 320, 48)])
+def test_layer_launch_lines(gpu, dt, T, N, K, B):
+    import torch
+    import paper_2512_02901_amd as f2
+    (cu, su, cw, sw), d, rng = layer(N, K, T, gpu)
+    if dt == "i8":
+        q = rng.integers(-127, 128, (B, K, 2)).astype(np.int8)
+        f = rng.uniform(0.001, 0.02, B).astype(np.float32)
+        y = host(f2.wl_matmul(*d, dev(q, gpu), dev(f, gpu)))
+        want = oracle.wl_matmul_int8(cu, su, cw, sw, q, f)
+        tol = 1e-6  # exact integers; the GEMM combines its axis sums in float32
+    else:
+        x = synth.bf16_round_complex(rng.standard_normal((B, K)) + 1j * rng.standard_normal((B, K)))
+        xd = dev(np.stack([x.real, x.imag], -1).astype(np.float32), gpu).to(torch.bfloat16)
+        y = host(f2.wl_matmul(*d, xd))
+        want = oracle.wl_matmul(cu, su, cw, sw, x)
+        tol = 3e-7  # 23 bits of the token's largest magnitude
+    assert np.linalg.norm(y - want) <= tol * np.linalg.norm(want)
+
+
 @pytest.mark.parametrize("B,K,off", [(1, 4, 0), (3, 2048, 0), (2, 8192, 0), (2, 8196, 0), (5, 1500, 1), (2, 6, 0),
                                      (3, 252, 0), (2, 256, 0), (3, 260, 0), (2, 512, 0), (3, 516, 0), (2, 1024, 0),
                                      (3, 1028, 0)])
