@@ -9,11 +9,11 @@
 // but the operand kernel, the product over K slices and the reduction of the
 // slices take 4 + 12 + 4 us.  Here a block owns 16 rows of a layer and its
 // kWaves waves split K in 256-code steps (wave w takes steps w, w + kWaves,
-// ...), so the shares of y meet in LDS, in double and in wave order.  A wave
-// encodes the digits of its own steps from the tokens as the caller has them
-// (a lane per half run and component), after the block has found the tokens'
-// largest magnitudes; the layers come as kernel arguments, not from the table
-// in memory, so that the first loads wait for nothing.
+// ...), so the float shares of y meet in LDS and are added there in double, in
+// wave order.  A wave encodes the digits of its own steps from the tokens as the
+// caller has them (a lane per half run and component), after the block has found
+// the tokens' largest magnitudes; the layers come as kernel arguments, not from
+// the table in memory, so that the first loads wait for nothing.
 #include "common.h"
 #include "decode_dev.h"
 #include "f4_operand.h"
@@ -288,33 +288,45 @@ void launch_split_f4_t(const SplitGroup& a, bool gs, unsigned blocks, hipStream_
 
 }  // namespace
 
-// Every block encodes its tokens itself, so the one launch costs more per row
-// block than the streaming product, against the two launches it saves.  It is
-// taken while the call's row blocks are at most this many per CU: 4 at T = 1
-// and for one or two tokens at T = 2, 3 for three or four, 2 at T >= 3 (whose
-// blocks have a CU to themselves).  One launch / streaming, us ("all seven" layers of a decoder
-// block):
-//   n = 2048, n_ff = 5504, T = 2
-//     q k v        384 row blocks   1 token  7.4 / 14.3, 2  8.4 / 14.9, 4 12.0 / 18.7
-//       G = 256                     1 token  8.4 / 14.8,                4 13.2 / 19.5
-//     gate, up     688              1 token 10.6 / 14.5, 2 12.1 / 15.6, 4 17.1 / 19.5
-//     q k v twice  768              1 token 10.9 / 15.0,                4 17.5 / 21.1
-//     all seven   1328              1 token 22.1 / 21.9, 2 25.5 / 23.9, 4 43.4 / 30.7
-//   n = 512, T = 2, all seven: n_ff = 5504, 848: 1 token 13.4 / 18.6, 4 22.3 / 22.1
-//                              n_ff = 8192, 1184: 1 token 18.1 / 22.6, 4 31.9 / 29.0
-//   n = 1024, n_ff = 5504, T = 1, all seven, 1008: 4 tokens 19.6 / 23.5
-//   n = 2048, T = 3, q k v, 384: 4 tokens 16.7 / 19.8; T = 4: 1 token 12.8 / 16.7
-//   n_ff = 5504, gate, up, 688: n = 1536, T = 3, 2 tokens 19.2 / 17.6;
-//                               n = 1024, T = 4, 2 tokens 17.7 / 16.7
-constexpr int64_t kSplitBlocksUnit = 256;  // one row block per CU
+// Every block encodes its tokens itself, over all of K, so the one launch costs
+// more per row block and 256-code step than the streaming product, against the
+// two launches it saves.  What it costs goes with the steps that the row blocks
+// of a CU take together (row blocks x steps / 256 CUs), so the call's are
+// bounded, by T, tokens and kind of scales; three and four tokens halve the
+// waves on a row block's steps, which bounds the steps of a layer too.  One
+// launch / streaming, us (n x k: rows x columns of a layer, w: steps a CU):
+//   T = 1  8 x 2048 x 8192, w 128    1 token 26 / 27, 2 tokens 34 / 31
+//          8192 x 8192, w 64         2 tokens 20 / 23, 3 30 / 31, 4 34 / 31
+//          4 x 2048 x 5504, w 44     4 tokens 24 / 28
+//   T = 2  8 x 2048 x 8192, w 128    1 token 37 / 37; 2 46 / 41, G = 256 52 / 53
+//          8192 x 8192, w 64         2 tokens 25 / 30
+//          4 x 2048 x 5504, w 44     4 tokens 30 / 28, G = 256 33 / 35
+//          4 x 2048 x 4096, w 32     4 tokens 23 / 26
+//          1024 x 8192, w 8, 32 steps, G = 256, 4 tokens 29 / 26; 2048 x 5504, 22 steps, 20 / 26
+//   T = 3  8192 x 8192, w 64         1 token 29 / 28; 4 x 2048 x 5504, w 44, 23 / 25
+//          4 x 2048 x 4096, w 32     4 tokens 30 / 26; 2 x 2048 x 5504, w 22, 22 / 26
+//   T = 4  8192 x 8192, w 64         1 token 33 / 36, 2 38 / 38
+//          4 x 2048 x 4096, w 32     2 tokens 24 / 25, G = 256 31 / 29
+//          4096 x 8192, w 32 in one block a CU, G = 256, 2 tokens 27 / 31
+//   16384 x 256, one step: the streaming product has no slices to reduce
+//          T = 1 1 token 7.4 / 8.5; T = 2 1 token 9.5 / 9.3, 2 9.9 / 9.4
+// and by the row blocks alone, whose fixed cost is the tokens' (q k v 384, gate
+// and up 688, all seven layers of a 2048-wide block 1328):
+//   T = 2  384 1 token 7.4 / 14.3, 4 tokens 12.0 / 18.7; 688 10.6 / 14.5, 17.1 / 19.5;
+//          1024 (8 x 2048 x 2048) 14 / 19, 24 / 24; 1328 22.1 / 21.9, 43.4 / 30.7
+//   T = 3  384 4 tokens 16.7 / 19.8; 688 (n = 1536) 2 tokens 19.2 / 17.6
+//   T = 4  384 1 token 12.8 / 16.7; 688 (n = 1024) 2 tokens 17.7 / 16.7
+constexpr int64_t kCUs = 256;
 
 bool f4_split_ok(const DecHeader& h, const DecLayer* tab) {
   if (h.mode != kModeBf16F4 || h.bands != 2 || h.n_layers > kSplitLayers) return false;
   if (h.B > (h.T <= 3 ? 4 : 2)) return false;
-  int64_t blocks = 0;
+  int64_t blocks = 0, work = 0;
+  int longest = 0;
   for (int i = 0; i < h.n_layers; ++i) {
-    if (tab[i].nk4 > kSplitMaxSteps) return false;
+    longest = tab[i].nk4 > longest ? tab[i].nk4 : longest;
     blocks += tab[i].nrb;
+    work += (int64_t)tab[i].nrb * tab[i].nk4;
     // all tokens are read before any output is written only where there are
     // two launches: outputs in the memory of the call's tokens go there
     const auto y0 = reinterpret_cast<uintptr_t>(tab[i].y), y1 = y0 + (uintptr_t)h.B * (uintptr_t)tab[i].N * 8;
@@ -323,7 +335,19 @@ bool f4_split_ok(const DecHeader& h, const DecLayer* tab) {
       if (y0 < x1 && x0 < y1) return false;
     }
   }
-  return blocks <= kSplitBlocksUnit * (h.T >= 3 ? 2 : h.T == 2 && h.B > 2 ? 3 : 4);
+  if (longest > kSplitMaxSteps) return false;
+  if (longest > 24 && h.B > 2 && (h.T > 1 || blocks < 64)) return false;
+  if (longest == 1 && blocks > 2 * kCUs && (h.T > 1 || h.B == 2)) return false;
+  if (blocks > kCUs * (h.T >= 3 ? 2 : h.T == 2 && h.B > 2 ? 3 : 4)) return false;
+  const bool gs = h.grouped != 0;
+  int64_t most;  // steps per CU
+  switch (h.T) {
+    case 1: most = h.B == 1 ? 128 : h.B <= 3 ? 64 : 48; break;
+    case 2: most = h.B == 1 ? 128 : h.B == 2 ? (gs ? 128 : 64) : (gs ? 48 : 40); break;
+    case 3: most = h.B <= 2 ? 48 : 24; break;
+    default: most = h.B == 1 ? 64 : gs && blocks > kCUs ? 24 : 48; break;
+  }
+  return work <= most * kCUs;
 }
 
 hipError_t launch_split_f4(const DecHeader& h, const DecLayer* tab, hipStream_t s) {

@@ -252,3 +252,31 @@ def test_group_fp4_one_launch_and_streaming(gpu, T, B, G):
         assert max(errs) <= 1e-6
         for a in args:
             a[6].fill_(float("nan"))
+
+
+@pytest.mark.parametrize("T,B,G,shapes", [
+    (2, 3, 0, [(40, 6144)]), (2, 3, 0, [(40, 6208)]), (1, 4, 256, [(1040, 6208)]), (1, 4, 256, [(1008, 6208)]),
+    (2, 2, 0, [(8192, 64)]), (2, 2, 0, [(8208, 64)]), (3, 4, 0, [(2048, 768), (2048, 768)]),
+    (3, 4, 0, [(4096, 3136)]), (4, 2, 256, [(4112, 3136)])])
+def test_group_fp4_launch_lines(gpu, T, B, G, shapes):
+    """Either side of the lines between the one launch and the streaming
+    product: steps of a layer, row blocks of one step, steps per CU."""
+    import torch
+    import paper_2512_02901_amd as f2
+    from oracle import groups as og
+    rng = np.random.default_rng((96, T, B, G, shapes[0][0], shapes[0][1]))
+    args, refs = [], []
+    for i, (N, K) in enumerate(shapes):
+        x = synth.bf16_round_complex(synth.activations(B, K, (97, i, B)))
+        cu, cw = (rng.integers(0, 4, (T, N, K)).astype(np.uint8) for _ in range(2))
+        sshape = (T, N, -(-K // G), 2) if G else (T, 2)
+        su, sw = (rng.uniform(0.01, 0.02, sshape).astype(np.float32) for _ in range(2))
+        y = torch.empty((B, N), dtype=torch.complex64, device=gpu)
+        args.append((f2.repack_tiled_fp4(dev(oracle.pack(cu), gpu)), dev(su, gpu),
+                     f2.repack_tiled_fp4(dev(oracle.pack(cw), gpu)), dev(sw, gpu), bf16_dev(x, gpu), None, y))
+        refs.append(og.wl_matmul_grouped(cu, su, cw, sw, x, G) if G else oracle.wl_matmul(cu, su, cw, sw, x))
+    f2.WlGroup(args, T=T, B=B, layout=f2.LAYOUT_TILED_FP4, group_size=G).run()
+    torch.cuda.synchronize()
+    errs = [rel_l2(host(a[6]), r) for a, r in zip(args, refs)]
+    print(f"T={T} B={B} G={G} {shapes}:", " ".join(f"{e:.2e}" for e in errs))
+    assert max(errs) <= 1e-6  # two digit bands, float sums: as for the one launch and the streaming product above
