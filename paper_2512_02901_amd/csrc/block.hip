@@ -531,7 +531,7 @@ __global__ __launch_bounds__(64 * KW * M) void block_product_kernel(SplitArgs a)
       f4_unit_digits(xv, S, 2, out);
       f4_store_unit(xop[wave], hr >> 1, 8, 0, comp, hr & 1, 2, out);
     }
-    __builtin_amdgcn_wave_barrier();  // the wave's own LDS: written above, read below, in order
+    wave_sync();  // the wave's operand: written above, read below
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
       v4i x0 = v4i{0, 0, 0, 0}, x1 = x0;
@@ -548,7 +548,7 @@ __global__ __launch_bounds__(64 * KW * M) void block_product_kernel(SplitArgs a)
         aI[p] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(xa, bi, aI[p], kFmtFp8, kFmtFp4, 0, 0, 0, 0);
       }
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
 #pragma unroll
     for (int p = 0; p < P; ++p) c[p] = cn[p];
   }

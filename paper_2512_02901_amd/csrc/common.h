@@ -8,6 +8,15 @@
 
 namespace fairy2i {
 
+// What the wave's lanes wrote to LDS before is what they read after: LDS serves
+// a wave in order, the fences keep the compiler's order (it sees one lane, whose
+// own stores and loads need not meet).
+__device__ inline void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---------------------------------------------------------------- to_wl ---
 hipError_t launch_to_widely_linear(const float* A, int64_t N, int64_t K, float2* U, float2* W,
                                    hipStream_t stream);

@@ -181,7 +181,7 @@ __global__ __launch_bounds__(64 * kWaves, T <= 2 ? 4 : 2) void dec_split_f4_kern
         f4_unit_digits(xv, S[sl], 2, out);
         f4_store_unit(xop[wave], hr >> 1, 16, 8 * sl, comp, hr & 1, 2, out);
       }
-    __builtin_amdgcn_wave_barrier();  // the wave's own LDS: written above, read below, in order
+    wave_sync();  // the wave's operand: written above, read below
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
       const v4i y0 = *reinterpret_cast<const v4i*>(&xop[wave][((8 * kb + g) * 16 + li) * 16]);
@@ -197,7 +197,7 @@ __global__ __launch_bounds__(64 * kWaves, T <= 2 ? 4 : 2) void dec_split_f4_kern
         aI[p] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(xa, bi, cI, kFmtFp8, kFmtFp4, 0, 0, 0, 0);
       }
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     if constexpr (GS) {
 #pragma unroll
       for (int p = 0; p < P; ++p)

@@ -331,7 +331,7 @@ __global__ __launch_bounds__(64 * kWaves) void split_bf16_kernel(WlArgs a, bool 
     v4i cn[P];
     const bool more = s + kWaves < steps;
     if (more) codes.load(s + kWaves, cn);
-    __builtin_amdgcn_wave_barrier();  // the wave's own LDS: written above, read below, in order
+    wave_sync();  // the wave's operand: written above, read below
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
       const v4i xa = *reinterpret_cast<const v4i*>(&xop[wave][d][g][li]);
@@ -343,7 +343,7 @@ __global__ __launch_bounds__(64 * kWaves) void split_bf16_kernel(WlArgs a, bool 
         acc[p][1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(xa, bim, acc[p][1], 0, 0, 0);
       }
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     if (more) {
 #pragma unroll
       for (int p = 0; p < P; ++p) c[p] = cn[p];

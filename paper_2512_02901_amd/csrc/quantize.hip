@@ -146,15 +146,6 @@ __device__ inline void limbs_add(unsigned long long* acc, double v) {
   if (hi) atomicAdd(&acc[limb + 2], (unsigned long long)hi);
 }
 
-// What the wave's lanes wrote to LDS before is what they read after: LDS serves
-// a wave in order, the fences keep the compiler's order (a lane that adds
-// nothing could otherwise keep the zero it stored).
-__device__ inline void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // The residual of one entry after a stage whose code for it is k.
 __device__ inline void subtract_stage(double& re, double& im, uint32_t k, double s_re, double s_im) {
   const double s = (k & 1u) ? s_im : s_re;

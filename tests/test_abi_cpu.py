@@ -390,3 +390,17 @@ def test_quantiser_totals_ordered_before_the_arrival_count(tmp_path):
         adds, counts = ([i for i in atomics if ("sc0" in lines[i]) == r] for r in (False, True))
         assert adds and len(counts) == 2 and max(adds) < wait < min(counts)
         assert any(l.startswith("s_barrier") for l in lines[wait:min(counts)])
+
+
+def test_wave_local_lds_is_fenced():
+    """A wave barrier orders no memory for the compiler, which sees one lane:
+    lanes that write LDS words for other lanes of their wave to read put
+    wave_sync() (barrier and fences) between.  The one bare barrier stands
+    before reads in an asm with a memory clobber."""
+    from paper_2512_02901_amd import build
+    bare = {os.path.basename(p): open(p).read().count("__builtin_amdgcn_wave_barrier")
+            for p in build.sources() + [os.path.join(build.CSRC, "common.h"), os.path.join(build.CSRC, "decode_dev.h")]}
+    assert {k: v for k, v in bare.items() if v} == {"common.h": 1, "decode_split.hip": 1}
+    split = open(os.path.join(build.CSRC, "decode_split.hip")).read()
+    after = split[split.index("__builtin_amdgcn_wave_barrier"):]
+    assert after.index("lds_read4(") < after.index("split_bf16_kernel")
