@@ -9,9 +9,9 @@
 //   add_rmsnorm   residual add, RMSNorm over the 2n real components, bf16 out
 //   rope_append   rotary embedding as a complex rotation per head entry
 //                 (angles in double), key and value written to the caches
-//   attn_partial  per (head, 64-position slice): scores, slice max, slice
-//                 softmax sum and the slice's weighted sum of values
-//   attn_combine  the slices of a head merged in a fixed order, bf16 out
+//   attn_partial  per (head, run of 64 or more positions): scores, the run's
+//                 maximum, softmax sum and weighted sum of values
+//   attn_combine  the runs of a head merged in a fixed order, bf16 out
 //   swiglu        silu(Re g) Re u + i silu(Im g) Im u, bf16 out
 //   add           the final residual add
 // For one token with two digit bands (every block this library plans, up to
@@ -37,8 +37,8 @@ namespace fairy2i {
 
 namespace {
 
-constexpr int kAttnSlice = 64;   // positions per attention slice (one per lane)
-constexpr int kMaxAttnSlices = 4096;  // slices per head: their factors sit in LDS
+constexpr int kAttnRun = 64;  // positions of an attention block's shortest run
+constexpr int64_t kMaxContext = (int64_t)1 << 18;
 constexpr int kNormThreads = 256;
 
 __device__ inline uint16_t bf16_rne(float f) {
@@ -123,115 +123,127 @@ __global__ void rope_append_kernel(const float2* __restrict__ q, const float2* _
   v_cache[at] = v[i];
 }
 
-// One block of four waves per (64-position slice, head).  Scores: eight lanes
-// per position, which take a key row's 16-byte chunks in turn (128 bytes a
-// row and load, eight loads in flight), summed across the lanes, times scale;
-// then the slice's maximum m, e_t = exp(s_t - m) (kept in LDS) and
-// l = sum e_t.  Values: wave w takes positions 16 w .. 16 w + 15 of
-// o = sum_t e_t v_t, 16 bytes a lane, and the four waves' sums are added in
-// wave order.  From the scores on everything is in double (bound by memory,
-// the kernel has the time): the output is rounded to bf16, and a sum in float
+// One block of four waves per (run of positions, head).  Each wave takes every
+// fourth step of 16 / R positions of the run and keeps the running maximum m,
+// l = sum e^(s_t - m) and o = sum e^(s_t - m) v_t of its own, so nothing in the
+// walk waits for another wave.  Scores: 8 R lanes per position, which take a
+// key row's 16-byte chunks in turn (eight loads in flight a lane), summed
+// across the lanes, times scale.  Values: 16 bytes a lane, eight loads in
+// flight, asked for before the step's scores are formed, and the next step's
+// keys before its values are needed.  At the end the four waves' sums are
+// brought to one maximum and added in wave order.  From the scores on
+// everything is in double: the output is rounded to bf16, and a sum in float
 // puts a value next to a tie on the wrong side about once a token of 2048
-// entries.  Partial record per (head, slice): [m, l, o (2 dc doubles)].
+// entries.  Partial record per (head, run): [m, l, o (2 dc doubles)].
 constexpr int kAttnThreads = 256;
-template <int R>  // complex entries per lane in the value pass: dc <= 64 R
-__global__ __launch_bounds__(kAttnThreads, R == 1 ? 4 : 2) void attn_partial_kernel(const float2* __restrict__ q_rot,
-                                                                    const float2* __restrict__ k_cache,
-                                                                    const float2* __restrict__ v_cache, int dc,
-                                                                    int64_t n_ctx, int64_t max_ctx, double scale,
-                                                                    double2* __restrict__ part) {
-  __shared__ double es[kAttnSlice];
-  __shared__ double redm[kAttnThreads / 64], redl[kAttnThreads / 64];
-  __shared__ double2 ow[kAttnThreads / 64][64 * R];
-  const int h = blockIdx.y, sl = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t n0 = (int64_t)sl * kAttnSlice;
-  const int cnt = (int)min((int64_t)kAttnSlice, n_ctx - n0);
+template <int R>  // dc <= 64 R; R = 1, 2 or 4
+__global__ __launch_bounds__(kAttnThreads, R == 1 ? 4 : 3) void attn_partial_kernel(const float2* __restrict__ q_rot,
+                                                                       const float2* __restrict__ k_cache,
+                                                                       const float2* __restrict__ v_cache, int dc,
+                                                                       int n_ctx, int64_t max_ctx, int run,
+                                                                       double scale, double2* __restrict__ part) {
+#if defined(__HIP_DEVICE_COMPILE__)  // buffer-descriptor code: device pass only
+  constexpr int W = kAttnThreads / 64;
+  constexpr int LP = 8 * R, PR = 64 / LP, PS = 2 * PR;        // lanes a key row, rows a load, rows a step
+  constexpr int RPI = R == 1 ? 2 : 1, NR = R == 4 ? 2 : 1;    // value rows a load, loads a row
+  constexpr int VL = PS / RPI, LV = 64 / RPI;                 // loads a step (of NR), lanes a value row
+  __shared__ double2 qs[32 * R][2];  // in registers over the walk it would spill
+  __shared__ double es[W][PS];
+  __shared__ double redm[W], redl[W];
+  __shared__ double2 ow[W][64 * R];
+  const int h = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
+  const int t_end = min((int)(blockIdx.x + 1) * run, n_ctx), nf4 = dc / 2;
+  // Rows of the head from position t to the run's end (past it: zeros), each
+  // load's own descriptor: scalar arithmetic in place of sixteen vector offsets
+  const uint32_t row = 8u * (uint32_t)dc;  // at most 2 KB, positions below 2^18: 32 bits
   const float2* kh = k_cache + (int64_t)h * max_ctx * dc;
   const float2* vh = v_cache + (int64_t)h * max_ctx * dc;
-  const float4* qh = reinterpret_cast<const float4*>(q_rot + (int64_t)h * dc);
-  const int p = tid >> 3, qd = tid & 7, nf4 = dc / 2;
-  double acc[2] = {0.0, 0.0};
-#pragma unroll 1
-  for (int j0 = qd; j0 < nf4; j0 += 32) {
-    float4 kv[2][4], qv[4];
+  auto rows_from = [&](const float2* head, int t) {
+    return make_rsrc(uniform_ptr(head + (int64_t)t * dc), t < t_end ? (uint32_t)(t_end - t) * row : 0u);
+  };
+  const int p = lane / LP, qd = lane % LP, vr = lane / LV, vj = lane % LV;
+  uint32_t koff[4], voff[NR];  // of the lane's chunks
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int j = j0 + 8 * u;
+  for (int u = 0; u < 4; ++u) koff[u] = qd + LP * u < nf4 ? 16u * (uint32_t)(qd + LP * u) + (uint32_t)p * row : kOob;
 #pragma unroll
-      for (int hf = 0; hf < 2; ++hf) {
-        const int t = p + 32 * hf;
-        kv[hf][u] = t < cnt && j < nf4 ? reinterpret_cast<const float4*>(kh + (n0 + t) * dc)[j] : make_float4(0.f, 0.f, 0.f, 0.f);
-      }
-      qv[u] = j < nf4 ? qh[j] : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
+  for (int r = 0; r < NR; ++r) voff[r] = vj + LV * r < nf4 ? 16u * (uint32_t)(vj + LV * r) + (uint32_t)vr * row : kOob;
+  v4f kv[2][4], vv[VL][NR];
+  auto load_keys = [&](int t) {
 #pragma unroll
     for (int u = 0; u < 4; ++u)
 #pragma unroll
-      for (int hf = 0; hf < 2; ++hf) {
-        acc[hf] = fma((double)qv[u].x, (double)kv[hf][u].x, acc[hf]);
-        acc[hf] = fma((double)qv[u].y, (double)kv[hf][u].y, acc[hf]);
-        acc[hf] = fma((double)qv[u].z, (double)kv[hf][u].z, acc[hf]);
-        acc[hf] = fma((double)qv[u].w, (double)kv[hf][u].w, acc[hf]);
-      }
-  }
-  // the first values are asked for before the scores are reduced (all 16
-  // positions; for wide heads four: there are no registers for more)
-  constexpr int LPR = R == 1 ? 32 : 64, RPI = 64 / LPR, NR = R == 1 ? 1 : 2;  // lanes a row, rows and loads of one
-  constexpr int VL = R == 1 ? 8 : 4;
-  const int pb = 16 * wave, vj = lane % LPR, vr = lane / LPR;
-  float4 vv[VL][NR];
-  auto load_values = [&](int t0) {
+      for (int hf = 0; hf < 2; ++hf) kv[hf][u] = __builtin_bit_cast(v4f, buf_load16(rows_from(kh, t + PR * hf), koff[u]));
+  };
+  auto load_values = [&](int t) {
 #pragma unroll
     for (int u = 0; u < VL; ++u)
 #pragma unroll
-      for (int r = 0; r < NR; ++r) {
-        const int t = pb + t0 + u * RPI + vr, j = vj + LPR * r;
-        vv[u][r] = t < cnt && j < nf4 ? reinterpret_cast<const float4*>(vh + (n0 + t) * dc)[j] : make_float4(0.f, 0.f, 0.f, 0.f);
-      }
+      for (int r = 0; r < NR; ++r) vv[u][r] = __builtin_bit_cast(v4f, buf_load16(rows_from(vh, t + u * RPI), voff[r]));
   };
-  load_values(0);
-  double s[2];
-#pragma unroll
-  for (int hf = 0; hf < 2; ++hf) {
-    acc[hf] += __shfl_xor(acc[hf], 1);
-    acc[hf] += __shfl_xor(acc[hf], 2);
-    acc[hf] += __shfl_xor(acc[hf], 4);
-    s[hf] = p + 32 * hf < cnt ? acc[hf] * scale : -INFINITY;
+  int t0 = (int)blockIdx.x * run + PS * wave;
+  if (t0 < t_end) load_keys(t0);
+  for (int j = tid; j < 32 * R; j += kAttnThreads) {
+    const float4 q = j < nf4 ? reinterpret_cast<const float4*>(q_rot + (int64_t)h * dc)[j] : make_float4(0.f, 0.f, 0.f, 0.f);
+    qs[j][0] = make_double2(q.x, q.y);
+    qs[j][1] = make_double2(q.z, q.w);
   }
-  double m = wave_max(fmax(s[0], s[1]));
-  if (lane == 0) redm[wave] = m;
   __syncthreads();
-  m = fmax(fmax(redm[0], redm[1]), fmax(redm[2], redm[3]));
-  double lw = 0.0;
-#pragma unroll
-  for (int hf = 0; hf < 2; ++hf) {
-    const double e = p + 32 * hf < cnt ? exp(s[hf] - m) : 0.0;
-    if (qd == 0) {
-      es[p + 32 * hf] = e;
-      lw += e;
-    }
-  }
-  lw = wave_sum(lw);
-  if (lane == 0) redl[wave] = lw;
-  __syncthreads();
-  const double l = ((redl[0] + redl[1]) + redl[2]) + redl[3];
-  double o[NR][4];
+  double m = -INFINITY, l = 0.0, o[NR][4];
 #pragma unroll
   for (int r = 0; r < NR; ++r) o[r][0] = o[r][1] = o[r][2] = o[r][3] = 0.0;
-#pragma unroll 1
-  for (int t0 = 0; t0 < 16; t0 += VL * RPI) {
-    if (t0 > 0) load_values(t0);
+  while (t0 < t_end) {
+    load_values(t0);
+    double s[2] = {0.0, 0.0};
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const double2 q01 = qs[qd + LP * u][0], q23 = qs[qd + LP * u][1];
+      const double q[4] = {q01.x, q01.y, q23.x, q23.y};
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) s[hf] = fma(q[k], (double)kv[hf][u][k], s[hf]);
+    }
+    const int t1 = t0 + W * PS;
+    __builtin_amdgcn_sched_barrier(0);  // the keys' registers, for the next step's
+    load_keys(t1);                      // past the run: zeros
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf) {
+#pragma unroll
+      for (int off = 1; off < LP; off <<= 1) s[hf] += __shfl_xor(s[hf], off);
+      s[hf] = t0 + p + PR * hf < t_end ? s[hf] * scale : -INFINITY;
+    }
+    double mn = fmax(s[0], s[1]);
+#pragma unroll
+    for (int off = LP; off < 64; off <<= 1) mn = fmax(mn, __shfl_xor(mn, off));
+    mn = fmax(m, mn);
+    const double ref = mn == -INFINITY ? 0.0 : mn;  // no score above -infinity yet: every e is 0
+    const double f = exp(m - ref);
+    l *= f;
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf) {
+      const double e = exp(s[hf] - ref);
+      l += e;  // of the lane's positions, alike in the LP lanes of one
+      if (qd == 0) es[wave][p + PR * hf] = e;
+    }
+    wave_sync();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) o[r][k] *= f;
 #pragma unroll
     for (int u = 0; u < VL; ++u) {
-      const double w = es[pb + t0 + u * RPI + vr];  // 0 past cnt
+      const double w = es[wave][u * RPI + vr];  // 0 past the run
 #pragma unroll
       for (int r = 0; r < NR; ++r) {
-        o[r][0] = fma(w, (double)vv[u][r].x, o[r][0]);
-        o[r][1] = fma(w, (double)vv[u][r].y, o[r][1]);
-        o[r][2] = fma(w, (double)vv[u][r].z, o[r][2]);
-        o[r][3] = fma(w, (double)vv[u][r].w, o[r][3]);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) o[r][k] = fma(w, (double)vv[u][r][k], o[r][k]);
       }
     }
+    wave_sync();
+    m = mn;
+    t0 = t1;
   }
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
@@ -240,28 +252,45 @@ __global__ __launch_bounds__(kAttnThreads, R == 1 ? 4 : 2) void attn_partial_ker
       for (int k = 0; k < 4; ++k) o[r][k] += __shfl_xor(o[r][k], 32);
     }
     if (vr == 0) {
-      ow[wave][2 * (vj + LPR * r)] = make_double2(o[r][0], o[r][1]);
-      ow[wave][2 * (vj + LPR * r) + 1] = make_double2(o[r][2], o[r][3]);
+      ow[wave][2 * (vj + LV * r)] = make_double2(o[r][0], o[r][1]);
+      ow[wave][2 * (vj + LV * r) + 1] = make_double2(o[r][2], o[r][3]);
     }
   }
+  l = wave_sum(qd == 0 ? l : 0.0);
+  if (lane == 0) {
+    redm[wave] = m;
+    redl[wave] = l;
+  }
   __syncthreads();
-  double2* rec = part + ((int64_t)h * gridDim.x + sl) * (1 + dc);
-  if (tid == 0) rec[0] = make_double2(m, l);
+  double M = redm[0];
+#pragma unroll
+  for (int w = 1; w < W; ++w) M = fmax(M, redm[w]);
+  const double ref = M == -INFINITY ? 0.0 : M;
+  double f[W], L = 0.0;
+#pragma unroll
+  for (int w = 0; w < W; ++w) {
+    f[w] = exp(redm[w] - ref);  // 0 for a wave without positions
+    L = fma(redl[w], f[w], L);
+  }
+  double2* rec = part + ((int64_t)h * gridDim.x + blockIdx.x) * (1 + dc);
+  if (tid == 0) rec[0] = make_double2(M, L);
   for (int j = tid; j < dc; j += kAttnThreads) {
-    double2 a = ow[0][j];
-    for (int w = 1; w < kAttnThreads / 64; ++w) {
-      a.x += ow[w][j].x;
-      a.y += ow[w][j].y;
+    double2 a = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      a.x = fma(ow[w][j].x, f[w], a.x);
+      a.y = fma(ow[w][j].y, f[w], a.y);
     }
     rec[1 + j] = a;
   }
+#endif
 }
 
 // Per head: M = max_s m_s, f_s = e^(m_s - M) (in LDS), L = sum_s l_s f_s,
-// o_j = sum_s o_{s,j} f_s / L, wave w adding slices w, w + 4, ... and the
+// o_j = sum_s o_{s,j} f_s / L over the runs s, wave w adding w, w + 4, ... and the
 // waves' sums added in wave order; written as bf16 pairs at the head's
 // entries.  (A kernel of its own: merged by the block that ends last for its
-// head, every slice's block waits for its record and for its count, 18.4 us
+// head, every run's block waits for its record and for its count, 18.4 us
 // at context 2048 and 36.3 at 4096 in all, against 14.2 + 4.7 and 25.4 + 4.7.)
 template <int R>
 __global__ __launch_bounds__(kAttnThreads) void attn_combine_kernel(const double2* __restrict__ part, int ns, int dc,
@@ -272,10 +301,10 @@ __global__ __launch_bounds__(kAttnThreads) void attn_combine_kernel(const double
   const int h = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int rl = 1 + dc;
   const double2* ph = part + (int64_t)h * ns * rl;
-  // every wave's first eight slices (of an entry a lane) and every thread's
+  // every wave's first eight runs (of an entry a lane) and every thread's
   // first (m, l) in one round of loads
   double2 ov[8];
-  auto load_slices = [&](int i0, int r) {
+  auto load_runs = [&](int i0, int r) {
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const int i = i0 + 4 * u, j = lane + 64 * r;
@@ -283,7 +312,7 @@ __global__ __launch_bounds__(kAttnThreads) void attn_combine_kernel(const double
     }
   };
   const double2 ml0 = tid < ns ? ph[(int64_t)tid * rl] : make_double2(-INFINITY, 0.0);
-  load_slices(wave, 0);
+  load_runs(wave, 0);
   double M = ml0.x;
   for (int i = tid + kAttnThreads; i < ns; i += kAttnThreads) M = fmax(M, ph[(int64_t)i * rl].x);
   M = wave_max(M);
@@ -305,7 +334,7 @@ __global__ __launch_bounds__(kAttnThreads) void attn_combine_kernel(const double
   for (int r = 0; r < R; ++r) {
     double2 a = make_double2(0.0, 0.0);
     for (int i0 = wave; i0 < ns; i0 += 32) {
-      if (r > 0 || i0 != wave) load_slices(i0, r);
+      if (r > 0 || i0 != wave) load_runs(i0, r);
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         const int i = i0 + 4 * u;
@@ -682,7 +711,7 @@ bool block_desc_ok(const fairy2i_block_desc* d) {
   if (!d || d->n <= 0 || d->n_ff <= 0 || d->n_heads <= 0 || d->max_ctx <= 0) return false;
   if (d->n % d->n_heads != 0 || d->n / d->n_heads > 256 || (d->n / d->n_heads) % 2 != 0) return false;
   if (d->n % 64 != 0 || d->n_ff % 64 != 0) return false;
-  if (d->n > (1 << 24) || d->n_ff > (1 << 24) || d->max_ctx > (int64_t)kAttnSlice * kMaxAttnSlices) return false;
+  if (d->n > (1 << 24) || d->n_ff > (1 << 24) || d->max_ctx > kMaxContext) return false;
   if (d->T < 1 || d->T > FAIRY2I_MAX_STAGES || !(d->eps >= 0.0f) || !(d->rope_base > 0.0)) return false;
   return true;
 }
@@ -725,7 +754,7 @@ int group_layers(const fairy2i_block_desc* d, int gi, char* ws, const BlockLayou
 bool block_layout(const fairy2i_block_desc* d, BlockLayout& L) {
   const size_t n = (size_t)d->n, f = (size_t)d->n_ff;
   const size_t H = (size_t)d->n_heads, dc = n / H;
-  const size_t slices = ((size_t)d->max_ctx + kAttnSlice - 1) / kAttnSlice;
+  const size_t slices = ((size_t)d->max_ctx + kAttnRun - 1) / kAttnRun;
   size_t o = 0;
   auto take = [&](size_t bytes) { const size_t at = o; o += align256(bytes); return at; };
   L.z = take(n * 4);
@@ -755,23 +784,32 @@ bool block_layout(const fairy2i_block_desc* d, BlockLayout& L) {
 
 inline fairy2i_status hip_st(hipError_t e) { return e == hipSuccess ? FAIRY2I_OK : FAIRY2I_ERR_HIP; }
 
-void launch_attention(const BlockPlanHeader* hdr, float2* kc, float2* vc, int64_t pos, hipStream_t s) {
-  const int n = (int)hdr->n, H = hdr->n_heads, dc = n / H;
-  const int64_t n_ctx = pos + 1;
-  const int slices = (int)((n_ctx + kAttnSlice - 1) / kAttnSlice);
-  const double scale = 1.0 / sqrt((double)(2 * dc));
-  const dim3 grid(slices, H), heads(H), block(kAttnThreads);
-  const size_t lds = sizeof(double) * (size_t)slices;
-  uint32_t* o = reinterpret_cast<uint32_t*>(hdr->o);
-  if (dc <= 64) {
-    hipLaunchKernelGGL(attn_partial_kernel<1>, grid, block, 0, s, hdr->q_rot, kc, vc, dc, n_ctx, hdr->max_ctx, scale,
-                       hdr->part);
-    hipLaunchKernelGGL(attn_combine_kernel<1>, heads, block, lds, s, hdr->part, slices, dc, o);
-  } else {
-    hipLaunchKernelGGL(attn_partial_kernel<4>, grid, block, 0, s, hdr->q_rot, kc, vc, dc, n_ctx, hdr->max_ctx, scale,
-                       hdr->part);
-    hipLaunchKernelGGL(attn_combine_kernel<4>, heads, block, lds, s, hdr->part, slices, dc, o);
-  }
+// Positions a block takes: 64 while the heads' blocks are resident at once (four
+// a CU, three of wide heads), at longer contexts what that many blocks walk, in
+// whole steps; at most 256 runs a head, whose merge is one block's.
+template <int R>
+int attn_run(int64_t n_ctx, int H) {
+  constexpr int kResident = 256 * (R == 1 ? 4 : 3);
+  const int64_t most = H >= kResident ? 1 : kResident / H < 256 ? kResident / H : 256;
+  const int64_t run = (n_ctx + most - 1) / most;
+  return run <= kAttnRun ? kAttnRun : (int)((run + 15) / 16 * 16);
+}
+
+template <int R>
+void launch_attention(const BlockPlanHeader* hdr, const float2* kc, const float2* vc, int64_t pos, hipStream_t s) {
+  const int H = hdr->n_heads, dc = (int)hdr->n / H, n_ctx = (int)pos + 1;
+  const int run = attn_run<R>(n_ctx, H), runs = (n_ctx + run - 1) / run;
+  hipLaunchKernelGGL(attn_partial_kernel<R>, dim3(runs, H), dim3(kAttnThreads), 0, s, hdr->q_rot, kc, vc, dc, n_ctx,
+                     hdr->max_ctx, run, 1.0 / sqrt((double)(2 * dc)), hdr->part);
+  hipLaunchKernelGGL(attn_combine_kernel<R>, dim3(H), dim3(kAttnThreads), sizeof(double) * (size_t)runs, s, hdr->part,
+                     runs, dc, reinterpret_cast<uint32_t*>(hdr->o));
+}
+
+void launch_attention(const BlockPlanHeader* hdr, const float2* kc, const float2* vc, int64_t pos, hipStream_t s) {
+  const int dc = (int)hdr->n / hdr->n_heads;
+  if (dc <= 64) launch_attention<1>(hdr, kc, vc, pos, s);
+  else if (dc <= 128) launch_attention<2>(hdr, kc, vc, pos, s);
+  else launch_attention<4>(hdr, kc, vc, pos, s);
 }
 
 // The fused path: six launches.

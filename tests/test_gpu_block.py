@@ -244,8 +244,8 @@ def test_block_general_path_wide_heads(gpu):
 @pytest.mark.parametrize("n,f,H,T,max_ctx,pos", [
     (128, 320, 2, 1, 16, 3),           # one 256-code step or two, most waves without one
     (192, 448, 3, 3, 70, 65),
-    (64, 64, 2, 4, 2200, 2111),        # 33 slices: a second round of the merge's loads
-    (64, 128, 2, 2, 16600, 16500),     # 258 slices: more than a merging block has threads
+    (64, 64, 2, 4, 2200, 2111),        # 33 runs: a second round of the merge's loads
+    (64, 128, 2, 2, 16600, 16500),     # more positions than 256 runs of 64: longer ones
     (2112, 2304, 33, 3, 130, 129),     # past 2048: several steps a wave, 16 waves, wider token strides
     (320, 2112, 5, 4, 16, 0),          # T = 4 down projection past 2048, one cached position
 ])
@@ -268,3 +268,52 @@ def test_block_fused_edges(gpu, n, f, H, T, max_ctx, pos):
     print(f"n {n} f {f} T {T} pos {pos}: bf16 flips {flips}")
     y2 = host(blk.decode(dev(x, gpu), dev(kc, gpu), dev(vc, gpu), pos))
     np.testing.assert_array_equal(y.view(np.uint32), y2.view(np.uint32))
+
+
+@pytest.mark.parametrize("n,H,pos", [
+    (1024, 512, 299),     # 2 entries a head, two runs: three steps a wave, the last one ragged
+    (2048, 32, 2047),     # 64 entries, the longest context of one step a wave
+    (2048, 32, 2048),     # one position more
+    (2048, 32, 5000),
+    (8448, 88, 999),      # 96 entries: wide heads, the general path
+    (8192, 64, 130),      # 128 entries, runs of 64: two steps a wave
+    (8192, 32, 3000),     # 256 entries
+    (64, 2, 40000),       # 256 runs a head
+])
+@pytest.mark.parametrize("hidden", [0, 130])
+def test_block_attention_runs(gpu, n, H, pos, hidden):
+    """The attention at the edges of its runs, from the block's own rotated
+    query and caches, against 64-bit softmax; with the scores of the first
+    ``hidden`` positions at minus infinity (a wave or a run without a finite
+    score adds nothing).  One rounding to bf16: at most 2^-8 of each value."""
+    import torch
+    import paper_2512_02901_amd as f2
+    f, T, dc = 64, 1, n // H
+    g = torch.Generator(device=gpu)
+    g.manual_seed(n + pos)
+    w = {}
+    for name, (N, K) in shapes(n, f).items():
+        cu, cw = (f2.repack_tiled_fp4(torch.randint(0, 256, (T, N, K // 4), generator=g, device=gpu, dtype=torch.uint8))
+                  for _ in range(2))
+        s = torch.full((T, 2), 0.5 / K ** 0.5, device=gpu)
+        w[name] = (cu, s, cw, s)
+    gains = torch.ones(2 * n, device=gpu)
+    blk = f2.WlBlock(w, gains, gains, n=n, n_ff=f, n_heads=H, T=T, max_ctx=pos + 3)
+    x, k, v = (torch.view_as_complex(torch.randn((*s, 2), generator=g, device=gpu))
+               for s in ((1, n), (H, pos + 3, dc), (H, pos + 3, dc)))
+    blk.decode(x, k, v, pos)
+    q = blk.intermediates()["q_rot"].clone().view(H, dc)
+    low = min(hidden, pos)
+    k[:, :low, 0] = torch.complex(-torch.sign(q.real[:, :1]) * float("inf"), k[:, :low, 0].imag.clone())
+    k[:, pos + 1:], v[:, pos + 1:] = float("nan"), float("nan")  # past the context: never read
+    out = blk.decode(x, k, v, pos)
+    got = as_complex(blk.intermediates()["o"])
+    assert torch.equal(out, blk.decode(x, k, v, pos))
+    qd, kd = (torch.view_as_real(t).double().flatten(-2) for t in (q, k[:, :pos + 1]))
+    scores = torch.matmul(kd, qd.unsqueeze(-1)).squeeze(-1) / (2 * dc) ** 0.5
+    p = torch.softmax(scores, -1).unsqueeze(1)
+    vd = v[:, :pos + 1].to(torch.complex128)
+    want = torch.complex(torch.matmul(p, vd.real.contiguous()), torch.matmul(p, vd.imag.contiguous())).flatten().cpu().numpy()
+    assert np.isfinite(got).all()
+    for a, b in ((got.real, want.real), (got.imag, want.imag)):
+        assert (np.abs(a - b) <= 2.0 ** -8 * (1 + 2.0 ** -15) * np.abs(b)).all()
