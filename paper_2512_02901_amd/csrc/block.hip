@@ -135,13 +135,16 @@ __global__ void rope_append_kernel(const float2* __restrict__ q, const float2* _
 // everything is in double: the output is rounded to bf16, and a sum in float
 // puts a value next to a tie on the wrong side about once a token of 2048
 // entries.  Partial record per (head, run): [m, l, o (2 dc doubles)].
+// Bound by memory: 32 heads of 64 entries take 13.3 us for the 67 MB of context
+// 2048, 180 us for the 1.07 GB of 32768 (6.0 TB/s).  One block per 64 positions,
+// its waves meeting between scores and values, left four blocks a CU too few
+// bytes in flight: 14.1 us at 2048; block calls, us, with it / now: context 32768
+// 304 / 219, 262144 2172 / 1423, n = 4096 (64 heads) at 262144 4213 / 2826.
 constexpr int kAttnThreads = 256;
 template <int R>  // dc <= 64 R; R = 1, 2 or 4
-__global__ __launch_bounds__(kAttnThreads, R == 1 ? 4 : 3) void attn_partial_kernel(const float2* __restrict__ q_rot,
-                                                                       const float2* __restrict__ k_cache,
-                                                                       const float2* __restrict__ v_cache, int dc,
-                                                                       int n_ctx, int64_t max_ctx, int run,
-                                                                       double scale, double2* __restrict__ part) {
+__global__ __launch_bounds__(kAttnThreads, R == 1 ? 4 : 3) void attn_partial_kernel(
+    const float2* __restrict__ q_rot, const float2* __restrict__ k_cache, const float2* __restrict__ v_cache, int dc,
+    int n_ctx, int64_t max_ctx, int run, double scale, double2* __restrict__ part) {
 #if defined(__HIP_DEVICE_COMPILE__)  // buffer-descriptor code: device pass only
   constexpr int W = kAttnThreads / 64;
   constexpr int LP = 8 * R, PR = 64 / LP, PS = 2 * PR;        // lanes a key row, rows a load, rows a step
