@@ -651,11 +651,12 @@ __global__ __launch_bounds__(64 * KW * M) void block_product_kernel(SplitArgs a)
 // Waves per matrix: 8 (a step of 256 codes each up to K = 2048); 4 for the
 // two matrices of SwiGLU, so that two blocks fit a CU (with 8 each one does,
 // and 344 blocks take two rounds: 16.2 us against 11.4); 16 where K is
-// longer and one matrix's rows leave most of the chip idle (8 at T = 4, whose
-// sums take the registers).  The token takes E entries a thread.
+// longer and one matrix's rows leave most of the chip idle (8 from T = 3 on,
+// whose sums take the registers: with 16 the T = 3 kernel spills, blocks of
+// n = n_ff = 8192 184 us against 176, 178.8 in 13 launches; 4096, 8192 85 and 82).  The token takes E entries a thread.
 template <int T, int SRC, int OUT>
 void launch_block_product(const SplitArgs& a, hipStream_t s) {
-  constexpr int KW = OUT == kOutSwiglu ? 4 : 8, M = OUT == kOutSwiglu ? 2 : 1, KL = OUT == kOutAdd && T <= 3 ? 16 : KW;
+  constexpr int KW = OUT == kOutSwiglu ? 4 : 8, M = OUT == kOutSwiglu ? 2 : 1, KL = OUT == kOutAdd && T <= 2 ? 16 : KW;
   const dim3 grid((unsigned)(a.N / 16), OUT == kOutRope ? 3 : 1);
   if (a.K <= 2048)
     hipLaunchKernelGGL((block_product_kernel<T, KW, M, SRC, OUT, 4>), grid, dim3(512), 0, s, a);

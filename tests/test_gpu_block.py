@@ -246,7 +246,8 @@ def test_block_general_path_wide_heads(gpu):
     (192, 448, 3, 3, 70, 65),
     (64, 64, 2, 4, 2200, 2111),        # 33 runs: a second round of the merge's loads
     (64, 128, 2, 2, 16600, 16500),     # more positions than 256 runs of 64: longer ones
-    (2112, 2304, 33, 3, 130, 129),     # past 2048: several steps a wave, 16 waves, wider token strides
+    (2112, 2304, 33, 3, 130, 129),     # past 2048: several steps a wave, wider token strides
+    (2112, 2304, 33, 2, 16, 7),        # the same with 16 waves
     (320, 2112, 5, 4, 16, 0),          # T = 4 down projection past 2048, one cached position
 ])
 def test_block_fused_edges(gpu, n, f, H, T, max_ctx, pos):
