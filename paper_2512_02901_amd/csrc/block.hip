@@ -429,9 +429,11 @@ constexpr int kSrcNorm = 0, kSrcBf16 = 1;
 constexpr int kOutRope = 0, kOutAdd = 1, kOutSwiglu = 2;
 constexpr int kSplitMaxK = 8192;  // complex entries of a token the fused path takes
 
-// M matrices with KW waves each; a token of K <= E * threads entries.
+// M matrices with KW waves each; a token of K <= E * threads entries.  (T = 3:
+// 128 registers, so that two blocks fit a CU: with the 164 of q, k and v past
+// K = 2048 a block of n = 8192, n_ff = 1024 took 141 us, now 125.5.)
 template <int T, int KW, int M, int SRC, int OUT, int E>
-__global__ __launch_bounds__(64 * KW * M) void block_product_kernel(SplitArgs a) {
+__global__ __launch_bounds__(64 * KW * M, T == 3 ? 4 : 1) void block_product_kernel(SplitArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)  // buffer-descriptor code: device pass only
   constexpr int P = 2 * T, W = KW * M, NTH = 64 * W;
   __shared__ __attribute__((aligned(16))) uint32_t tokw[E * NTH];
@@ -653,7 +655,7 @@ __global__ __launch_bounds__(64 * KW * M) void block_product_kernel(SplitArgs a)
 // and 344 blocks take two rounds: 16.2 us against 11.4); 16 where K is
 // longer and one matrix's rows leave most of the chip idle (8 from T = 3 on,
 // whose sums take the registers: with 16 the T = 3 kernel spills, blocks of
-// n = n_ff = 8192 184 us against 176, 178.8 in 13 launches; 4096, 8192 85 and 82).  The token takes E entries a thread.
+// n = n_ff = 8192 184 us against 176; 4096, 8192 85 and 82).  The token takes E entries a thread.
 template <int T, int SRC, int OUT>
 void launch_block_product(const SplitArgs& a, hipStream_t s) {
   constexpr int KW = OUT == kOutSwiglu ? 4 : 8, M = OUT == kOutSwiglu ? 2 : 1, KL = OUT == kOutAdd && T <= 2 ? 16 : KW;
