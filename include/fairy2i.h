@@ -193,6 +193,10 @@ size_t fairy2i_wl_matmul_workspace_bytes(int64_t N, int64_t K, int32_t T, int64_
  * operands through LDS.  With K % 64 == 0 calls of few rows and tokens take
  * one launch instead, without the workspace.
  * Any other K runs a direct kernel without workspace.
+ * y may lie in the memory of x where the call has a workspace (every
+ * activation is then read before any output is written), for
+ * B <= FAIRY2I_MAX_DECODE_BATCH in that of x_scale too; otherwise it must not
+ * overlap an operand.
  * workspace: at least fairy2i_wl_matmul_workspace_bytes(...) bytes of
  * device memory (may be NULL when that is 0), contents ignored on entry.
  * Errors: FAIRY2I_ERR_NULL; FAIRY2I_ERR_SHAPE if N, K, B <= 0 or K % 4;
@@ -314,6 +318,7 @@ typedef struct fairy2i_wl_layer {
  * fairy2i_wl_matmul_group(table, table_device, stream) computes every layer's
  * y.  The workspace and both table copies must stay alive and unchanged while
  * calls that use them run; calls sharing a workspace must not overlap.
+ * Outputs may lie in the memory of the call's tokens, as above.
  * Results equal fairy2i_wl_matmul on each layer up to the float32 rounding
  * of the split-K sums (a one-layer call may cut K into more slices to fill
  * the GPU); repeated calls are bitwise identical.

@@ -137,13 +137,15 @@ bool one_launch_pays(const WlArgs& a) {
   return rb <= (T == 2 || (T == 3 && (steps >= 16 || B >= 4)) ? 2048 : T == 1 && B > 4 ? 1536 : 1024);
 }
 
-// The outputs lie in the memory of the activations (or their factors).
+// The outputs lie in the memory of the activations, or of the token factors
+// (B <= 16: the operand kernel reads those too; the prefill GEMM reads them as
+// it stores, so above 16 tokens outputs over them are not supported).
 bool outputs_over_inputs(const WlArgs& a) {
   const auto at = [](const void* p) { return reinterpret_cast<uintptr_t>(p); };
   const uintptr_t o = at(a.y), on = (uintptr_t)8 * a.B * a.N;
   const uintptr_t xn = (uintptr_t)2 * a.B * a.K * (a.dtype == FAIRY2I_ACT_I8 ? 1 : 2);
   const auto meets = [&](const void* p, uintptr_t n) { return p && o < at(p) + n && at(p) < o + on; };
-  return meets(a.x, xn) || meets(a.x_scale, (uintptr_t)4 * a.B);
+  return meets(a.x, xn) || (a.B <= FAIRY2I_MAX_DECODE_BATCH && meets(a.x_scale, (uintptr_t)4 * a.B));
 }
 
 // The operand kernel, product and reduction of a one-layer decode call: every

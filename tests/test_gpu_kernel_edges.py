@@ -322,3 +322,25 @@ def test_outputs_over_tokens(gpu, dt, B):
     tokens.copy_(x)
     got = product(tokens, mem)
     assert np.linalg.norm(got - want) <= 1e-6 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("B", [1, 16])
+def test_outputs_over_token_factors(gpu, B):
+    """Outputs written over the int8 tokens' factors: read before as well, up to
+    16 tokens."""
+    import torch
+    import paper_2512_02901_amd as f2
+    N, K, T = 512, 1024, 2
+    rng = np.random.default_rng((96, B))
+    w = []
+    for _ in range(2):
+        w += [dev(rng.integers(0, 256, (T, N, K // 4)).astype(np.uint8), gpu),
+              dev(rng.uniform(0.01, 0.02, (T, 2)).astype(np.float32), gpu)]
+    q, xs = f2.quantize_act_int8(dev((rng.standard_normal((B, K)) + 1j * rng.standard_normal((B, K))).astype(np.complex64), gpu))
+    want = host(f2.wl_matmul(*w, q, xs))
+    for first in (0, 2 * B * N - B):  # the factors at the start and at the end of the outputs
+        y = torch.empty((B, N), dtype=torch.complex64, device=gpu)
+        factors = torch.view_as_real(y).view(-1)[first:first + B]
+        factors.copy_(xs)
+        got = host(f2.wl_matmul(*w, q, factors, out=y))
+        assert np.linalg.norm(got - want) <= 1e-6 * np.linalg.norm(want)
