@@ -344,3 +344,130 @@ def test_outputs_over_token_factors(gpu, B):
         factors.copy_(xs)
         got = host(f2.wl_matmul(*w, q, factors, out=y))
         assert np.linalg.norm(got - want) <= 1e-6 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("T", [1, 2, 3, 4])
+@pytest.mark.parametrize("B", [2, 5])
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_float_layer_infinity_values(gpu, dt, B, T):
+    """One infinite activation: every other token of its block keeps the values
+    of a finite call, and its own token's outputs are those plus the terms
+    +-s infinity that the codes of that column give (opposite ones: undefined)."""
+    import torch
+    import paper_2512_02901_amd as f2
+    N, K, col = 7, 20, 13
+    (cu, su, cw, sw), d, rng = layer(N, K, T, gpu)
+    x = synth.bf16_round_complex(rng.standard_normal((B, K)) + 1j * rng.standard_normal((B, K))).astype(np.complex64)
+    bad = B - 2
+    x.real[bad, col] = 0
+    want = oracle.wl_matmul(cu, su, cw, sw, x)
+    R = np.abs(oracle.dequantize(cu, su)) + np.abs(oracle.dequantize(cw, sw))
+    bound = 2.0 ** -24 * (K / 64 + 14) * (np.abs(x) @ R.T)
+    # Re x enters Re y through codes +-1 and Im y through +-i, of both matrices
+    inf = np.zeros((N, 2))
+    with np.errstate(invalid="ignore"):
+        for c in (cu, cw):
+            for t in range(T):
+                k = c[t, :, col].astype(int)
+                inf[np.arange(N), k & 1] += np.where(k & 2, -np.inf, np.inf)
+    x.real[bad, col] = np.inf
+    xd = dev(x, gpu) if dt == "f32" else dev(np.stack([x.real, x.imag], -1).astype(np.float32), gpu).to(torch.bfloat16)
+    y = host(f2.wl_matmul(*d, xd))
+    for b in range(B):
+        for part, (g, w) in enumerate(((y[b].real, want[b].real), (y[b].imag, want[b].imag))):
+            e = inf[:, part] if b == bad else np.zeros(N)
+            fin = e == 0
+            assert (np.abs(g - w)[fin] <= bound[b][fin]).all()
+            np.testing.assert_array_equal(g[~fin], e[~fin])
+
+
+def one_launch_calls(gpu, seed):
+    """(name, inputs, call) of the one-launch routes and the table kernel; a call
+    writes the same outputs each time."""
+    import torch
+    import paper_2512_02901_amd as f2
+    g = torch.Generator(device=gpu)
+    g.manual_seed(seed)
+
+    def weights(T, N, K):
+        return [t for _ in range(2) for t in
+                (torch.randint(0, 256, (T, N, K // 4), generator=g, device=gpu, dtype=torch.uint8),
+                 0.01 + 0.01 * torch.rand((T, 2), generator=g, device=gpu))]
+
+    def out(B, N):
+        return torch.empty((B, N), dtype=torch.complex64, device=gpu)
+
+    def layer_call(T, N, K, x, xs=None):
+        w, y = weights(T, N, K), out(x.shape[0], N)
+        dt = f2.ACT_I8 if xs is not None else f2.ACT_BF16 if x.dtype == torch.bfloat16 else f2.ACT_F32
+        ws = torch.empty(max(1, f2.wl_matmul_workspace_bytes(N, K, T, x.shape[0], dt)), dtype=torch.uint8, device=gpu)
+        return lambda: f2.wl_matmul(*w, x, xs, out=y, workspace=ws)
+
+    def bf16(B, K):
+        return torch.randn((B, K, 2), generator=g, device=gpu).to(torch.bfloat16)
+
+    calls = []
+    x = bf16(3, 1024)
+    calls.append(("bf16", x, layer_call(2, 272, 1024, x)))
+    q, xs = f2.quantize_act_int8(bf16(40, 1024))
+    calls.append(("int8", xs, layer_call(2, 272, 1024, q, xs)))
+    z = torch.view_as_complex(torch.randn((3, 500, 2), generator=g, device=gpu))
+    calls.append(("table", z, layer_call(3, 130, 500, z)))
+    t = bf16(4, 1024)
+    layers = []
+    for N in (272, 512):
+        cu, su, cw, sw = weights(2, N, 1024)
+        layers.append((f2.repack_tiled_fp4(cu), su, f2.repack_tiled_fp4(cw), sw, t, None, out(4, N)))
+    plan = f2.WlGroup(layers, T=2, B=4, layout=f2.LAYOUT_TILED_FP4)
+
+    def run():
+        plan.run()
+        return torch.cat([l[6] for l in layers], 1)
+    calls.append(("group", t, run))
+    return calls
+
+
+def test_one_launch_under_capture(gpu):
+    """A captured call, replayed with other tokens in the same memory and eager
+    work between the replays, gives what the eager call gives."""
+    import torch
+    for name, x, call in one_launch_calls(gpu, 31):
+        call()
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            y = call()
+        for i in range(3):
+            x.copy_(x.roll(1, -1) if name == "int8" else x.roll(7 + i, 1))
+            want = call().clone()
+            y.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(y, want), (name, i)
+
+
+def test_one_launch_from_two_threads(gpu):
+    """Two threads, each on a stream of its own with its own operands."""
+    import threading
+    import torch
+    calls = [one_launch_calls(gpu, 41), one_launch_calls(gpu, 42)]
+    want = [[call().clone() for _, _, call in c] for c in calls]
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(i):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream(gpu)) as _:
+                for _ in range(20):
+                    for (name, _, call), w in zip(calls[i], want[i]):
+                        if not torch.equal(call(), w):
+                            wrong.append((i, name))
+        except Exception as e:  # an assertion in a thread would be lost
+            wrong.append((i, repr(e)))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong, wrong
