@@ -180,14 +180,14 @@ size_t fairy2i_wl_matmul_workspace_bytes(int64_t N, int64_t K, int32_t T, int64_
  * as produced by fairy2i_quantize_act_int8) and y[b] is multiplied by it;
  * for the float dtypes x_scale must be NULL.
  * y: complex64 [B][N] output.
- * Accumulation is exact integer arithmetic on the matrix cores, or float32
- * in the vector kernel, always in a fixed order: results are bitwise
- * reproducible run to run.
+ * Accumulation is exact integer arithmetic on the matrix cores, or on the
+ * vector units float32 for float32 activations and double for bf16, always in
+ * a fixed order: results are bitwise reproducible run to run.
  * B <= FAIRY2I_MAX_DECODE_BATCH: bf16 and int8 activations with
  * K % 64 == 0 go to the int8 matrix cores (bf16 tokens as a 23-bit block
  * fixed point, exact for every value within 2^14 of the token's largest
- * magnitude, smaller values rounded to that grid), other cases to a float32 /
- * int32 vector kernel.  Larger B needs FAIRY2I_ACT_I8; with K % 64 == 0 it
+ * magnitude, smaller values rounded to that grid), other cases to the vector
+ * units.  Larger B needs FAIRY2I_ACT_I8; with K % 64 == 0 it
  * runs the int8-MFMA prefill GEMM (sizes within 32-bit offsets): a workspace
  * holds the activations in the matrix-core operand layout and the GEMM streams
  * operands through LDS.  With K % 64 == 0 calls of few rows and tokens take

@@ -19,6 +19,13 @@
 // 128 x 128, T = 2, one token 9.5, now 4.0; 5504 x 5504, 16 tokens 829, now
 // 97.  Two or eight rows a block instead of four: 10.9 and 9.9 against 8.7 us
 // for 1001 x 1500, T = 2, 16 tokens, 147 and 107 for 5504 x 5504.)
+// bf16 activations: entries and sums in double.  Signed adds of 8-bit
+// significands round little (4e-8 to 9e-8 of the result for K 260 .. 16388 and
+// T 1 .. 4, where float32 entries and sums are 8e-8 to 2e-7 off); in double it
+// is 2.5e-8, the output's own rounding.  The tables are U's and W's 16 sums
+// apart, 256 bytes each that random indexes read without bank conflicts, added
+// per code: 5504 x 2052, T = 2, one token 11.7 us (256 blocks of 32 bytes 15.9),
+// 16 tokens 66; in float32 8.9 and 42, by signed adds 22 and 439.
 // A table entry of 0 times an infinite activation would be NaN where a code's
 // sign flips and adds give a finite sum, so a block that meets one recomputes
 // its outputs by those.
@@ -244,25 +251,34 @@ __device__ inline void load_four(const void* x, int64_t e0, bool vec, float (&re
 // l / (64 / NV).
 // (Recursion, so that every index is a constant: a loop over the halvings
 // became chains of selects, 9 us of a 128 x 128 call.)
-template <int NV, int OFF = 32>
-__device__ inline float wave_sums(const float (&v)[NV], int lane) {
+template <int NV, int OFF = 32, typename A>
+__device__ inline A wave_sums(const A (&v)[NV], int lane) {
   if constexpr (NV > 1) {
     const bool up = (lane & OFF) != 0;
-    float h[NV / 2];
+    A h[NV / 2];
 #pragma unroll
     for (int i = 0; i < NV / 2; ++i) {
-      const float keep = up ? v[i + NV / 2] : v[i], send = up ? v[i] : v[i + NV / 2];
+      const A keep = up ? v[i + NV / 2] : v[i], send = up ? v[i] : v[i + NV / 2];
       h[i] = keep + __shfl_xor(send, OFF);
     }
     return wave_sums<NV / 2, OFF / 2>(h, lane);
   } else if constexpr (OFF > 0) {
-    const float h[1] = {v[0] + __shfl_xor(v[0], OFF)};
+    const A h[1] = {v[0] + __shfl_xor(v[0], OFF)};
     return wave_sums<1, OFF / 2>(h, lane);
   } else {
     return v[0];
   }
 }
 
+// What table entries and sums are held in.
+template <int DT>
+struct TableTraits {
+  using acc_t = float;
+};
+template <>
+struct TableTraits<FAIRY2I_ACT_BF16> {
+  using acc_t = double;
+};
 // One output by signed adds (a token with infinite or undefined values): the
 // lanes of a wave take every 64th column.
 template <int DT, int T>
@@ -305,13 +321,17 @@ __device__ inline float2 signed_adds(const WlArgs& a, int64_t row, int64_t b, in
 
 template <int DT, int T, int TB>
 __global__ __launch_bounds__(kTableThreads) void gemv_table_kernel(WlArgs a, bool vec) {
+  using A = typename TableTraits<DT>::acc_t;
   constexpr int kTables = (T + 1) / 2;  // one per pair of stages
   constexpr int kWaves = kTableThreads / 64;
   constexpr int NV = kRows * (TB <= 1 ? 1 : TB <= 2 ? 2 : 4) * 2;  // sums of a lane, padded to a power of two
-  // (R11, R12, R21, R22) by U's code of the pair's first stage (bits 0, 1) and
-  // second (2, 3), W's (4, 5) and (6, 7)
-  __shared__ float4 table[kTables][256];
-  __shared__ float part[kWaves][NV];
+  // float: (R11, R12, R21, R22) by U's code of the pair's first stage (bits 0, 1)
+  // and second (2, 3), W's (4, 5) and (6, 7); double: (Re, Im) of U's 16 sums and
+  // of W's, whose 256 bytes a random index reads without bank conflicts
+  constexpr bool kWide = sizeof(A) == 8;
+  __shared__ float4 table[kWide ? 1 : kTables][kWide ? 1 : 256];
+  __shared__ double2 half[kWide ? kTables : 1][2][kWide ? 16 : 1];
+  __shared__ A part[kWaves][NV];
   __shared__ int odd_values;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t row0 = (int64_t)blockIdx.x * kRows, b0 = (int64_t)blockIdx.y * TB;
@@ -332,16 +352,21 @@ __global__ __launch_bounds__(kTableThreads) void gemv_table_kernel(WlArgs a, boo
         w[1] += kw & 1u ? dw : 0.0;
       }
     }
-    table[p][threadIdx.x] =
-        make_float4((float)(u[0] + w[0]), (float)(w[1] - u[1]), (float)(u[1] + w[1]), (float)(u[0] - w[0]));
+    if constexpr (kWide) {
+      if (threadIdx.x < 16) half[p][0][threadIdx.x] = make_double2(u[0], u[1]);
+      if (threadIdx.x % 16 == 0) half[p][1][threadIdx.x / 16] = make_double2(w[0], w[1]);
+    } else {
+      table[p][threadIdx.x] =
+          make_float4((float)(u[0] + w[0]), (float)(w[1] - u[1]), (float)(u[1] + w[1]), (float)(u[0] - w[0]));
+    }
   }
   __syncthreads();
 
-  float acc[kRows][TB][2];
+  A acc[kRows][TB][2];
 #pragma unroll
   for (int r = 0; r < kRows; ++r)
 #pragma unroll
-    for (int tb = 0; tb < TB; ++tb) acc[r][tb][0] = acc[r][tb][1] = 0.0f;
+    for (int tb = 0; tb < TB; ++tb) acc[r][tb][0] = acc[r][tb][1] = 0;
   float check = 0.0f;  // 0 times every activation: NaN if one is not finite
   const int64_t kb = a.K / 4, plane = a.N * kb;
   for (int64_t s = threadIdx.x; s < kb; s += kTableThreads) {
@@ -360,36 +385,56 @@ __global__ __launch_bounds__(kTableThreads) void gemv_table_kernel(WlArgs a, boo
 #pragma unroll
       for (int e = 0; e < 4; ++e) check = fmaf(im[tb][e], 0.0f, fmaf(re[tb][e], 0.0f, check));
     }
+    // (doubles a column at a time: all columns' conversions and blocks together
+    // take up to 290 registers)
 #pragma unroll
-    for (int r = 0; r < kRows; ++r)
+    for (int k = 0; k < 4 * kRows; ++k) {
+      const int r = kWide ? k % kRows : k / 4, e = kWide ? k / kRows : k % 4;
+      if (kWide && r == 0) __builtin_amdgcn_sched_barrier(0);
+      A v[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        float4 v;
-#pragma unroll
-        for (int p = 0; p < kTables; ++p) {
+      for (int p = 0; p < kTables; ++p) {
+        const int p2 = 2 * p + 1 < T ? 2 * p + 1 : T - 1;  // the pair's second stage, where there is one
+        A q[4];
+        if constexpr (kWide) {
+          uint32_t iu = (c[r][2 * p] >> (2 * e)) & 3u, iw = (c[r][T + 2 * p] >> (2 * e)) & 3u;
+          if (2 * p + 1 < T) {
+            iu |= ((c[r][p2] >> (2 * e)) & 3u) << 2;
+            iw |= ((c[r][T + p2] >> (2 * e)) & 3u) << 2;
+          }
+          const double2 u = half[p][0][iu], w = half[p][1][iw];
+          q[0] = u.x; q[1] = u.y; q[2] = w.x; q[3] = w.y;
+        } else {
           uint32_t i = ((c[r][2 * p] >> (2 * e)) & 3u) | (((c[r][T + 2 * p] >> (2 * e)) & 3u) << 4);
-          if (2 * p + 1 < T)
-            i |= (((c[r][2 * p + (2 * p + 1 < T)] >> (2 * e)) & 3u) << 2) |
-                 (((c[r][T + 2 * p + (2 * p + 1 < T)] >> (2 * e)) & 3u) << 6);
-          const float4 q = table[p][i];
-          v = p == 0 ? q : make_float4(v.x + q.x, v.y + q.y, v.z + q.z, v.w + q.w);
+          if (2 * p + 1 < T) i |= (((c[r][p2] >> (2 * e)) & 3u) << 2) | (((c[r][T + p2] >> (2 * e)) & 3u) << 6);
+          const float4 t = table[p][i];
+          q[0] = t.x; q[1] = t.y; q[2] = t.z; q[3] = t.w;
         }
 #pragma unroll
-        for (int tb = 0; tb < TB; ++tb) {
-          acc[r][tb][0] = fmaf(v.y, im[tb][e], fmaf(v.x, re[tb][e], acc[r][tb][0]));
-          acc[r][tb][1] = fmaf(v.w, im[tb][e], fmaf(v.z, re[tb][e], acc[r][tb][1]));
-        }
+        for (int j = 0; j < 4; ++j) v[j] = p == 0 ? q[j] : v[j] + q[j];
       }
+      if constexpr (kWide) {
+        const A u0 = v[0], u1 = v[1];
+        v[0] = u0 + v[2]; v[1] = v[3] - u1;
+        const A w0 = v[2];
+        v[2] = u1 + v[3]; v[3] = u0 - w0;
+      }
+#pragma unroll
+      for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          acc[r][tb][j] = fma(v[2 * j + 1], (A)im[tb][e], fma(v[2 * j], (A)re[tb][e], acc[r][tb][j]));
+    }
   }
   if (check != check) odd_values = 1;
 
-  float v[NV];
+  A v[NV];
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
     const int r = i / (NV / kRows), tb = (i / 2) % (NV / kRows / 2);
-    v[i] = tb < TB ? acc[r][tb < TB ? tb : 0][i & 1] : 0.0f;
+    v[i] = tb < TB ? acc[r][tb < TB ? tb : 0][i & 1] : (A)0;
   }
-  const float sum = wave_sums<NV>(v, lane);
+  const A sum = wave_sums<NV>(v, lane);
   if (lane % (64 / NV) == 0) part[wave][lane / (64 / NV)] = sum;
   __syncthreads();
   if (odd_values) {
@@ -405,13 +450,13 @@ __global__ __launch_bounds__(kTableThreads) void gemv_table_kernel(WlArgs a, boo
   if (threadIdx.x < NV / 2) {
     const int r = threadIdx.x / (NV / kRows / 2), tb = threadIdx.x % (NV / kRows / 2);
     if (tb < TB && b0 + tb < a.B && row0 + r < a.N) {
-      float yr = 0.0f, yi = 0.0f;
+      A yr = 0, yi = 0;
 #pragma unroll
       for (int w = 0; w < kWaves; ++w) {
         yr += part[w][2 * threadIdx.x];
         yi += part[w][2 * threadIdx.x + 1];
       }
-      a.y[(b0 + tb) * a.N + row0 + r] = make_float2(yr, yi);
+      a.y[(b0 + tb) * a.N + row0 + r] = make_float2((float)yr, (float)yi);
     }
   }
 }

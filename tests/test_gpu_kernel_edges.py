@@ -471,3 +471,19 @@ def test_one_launch_from_two_threads(gpu):
     for t in threads:
         t.join()
     assert not wrong, wrong
+
+
+@pytest.mark.parametrize("N,K,T,B", [(256, 260, 1, 4), (130, 1500, 2, 3), (67, 5508, 3, 16), (33, 16388, 4, 5), (5, 12, 2, 1)])
+def test_bf16_layer_rounded_once(gpu, N, K, T, B):
+    """bf16 tokens off the matrix cores: 8-bit significands times sums of scales,
+    in double, so the output's rounding to float32 is the error (2^-24 a value)."""
+    import torch
+    import paper_2512_02901_amd as f2
+    (cu, su, cw, sw), d, rng = layer(N, K, T, gpu)
+    x = synth.bf16_round_complex(rng.standard_normal((B, K)) + 1j * rng.standard_normal((B, K)))
+    xd = dev(np.stack([x.real, x.imag], -1).astype(np.float32), gpu).to(torch.bfloat16)
+    want = x.astype(np.complex128) @ oracle.dequantize(cu, su).astype(np.complex128).T
+    want += np.conj(x).astype(np.complex128) @ oracle.dequantize(cw, sw).astype(np.complex128).T
+    y = host(f2.wl_matmul(*d, xd)).astype(np.complex128)
+    for g, w in ((y.real, want.real), (y.imag, want.imag)):
+        assert (np.abs(g - w) <= 2.0 ** -24 * np.abs(w) + 2.0 ** -46 * np.abs(want).max()).all()
