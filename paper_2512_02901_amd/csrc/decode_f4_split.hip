@@ -9,11 +9,13 @@
 // but the operand kernel, the product over K slices and the reduction of the
 // slices take 4 + 12 + 4 us.  Here a block owns 16 rows of a layer and its
 // kWaves waves split K in 256-code steps (wave w takes steps w, w + kWaves,
-// ...), so the float shares of y meet in LDS and are added there in double, in
-// wave order.  A wave encodes the digits of its own steps from the tokens as the
-// caller has them (a lane per half run and component), after the block has found
-// the tokens' largest magnitudes; the layers come as kernel arguments, not from
-// the table in memory, so that the first loads wait for nothing.
+// ...); their shares of y are recombined in double (in float one-step layers lost
+// up to a fifth of their precision: 4.0e-8 -> 4.9e-8 of the result at K = 64,
+// T = 1, now 2.7e-8), meet in LDS and are added in wave order, so y is rounded
+// once.  A wave encodes the digits of its own steps from the tokens as the caller
+// has them (a lane per half run and component), after the block has found the
+// tokens' largest magnitudes; the layers come as kernel arguments, not from the
+// table in memory, so that the first loads wait for nothing.
 #include "common.h"
 #include "decode_dev.h"
 #include "f4_operand.h"
@@ -50,7 +52,7 @@ __global__ __launch_bounds__(64 * kWaves, T <= 2 ? 4 : 2) void dec_split_f4_kern
   // token past the last stay zero
   __shared__ __attribute__((aligned(16))) uint8_t xop[kWaves][16 * 16 * 16];
   __shared__ float tok_max[2 * TILES][KW];
-  __shared__ float2 part[KW][2 * TILES][17];
+  __shared__ double2 part[KW][2 * TILES][17];
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, li = lane & 15;
   const int wave = uniform(tid >> 6), tile = wave % TILES, kw = wave / TILES;
   int idx = 0;
@@ -218,7 +220,7 @@ __global__ __launch_bounds__(64 * kWaves, T <= 2 ? 4 : 2) void dec_split_f4_kern
   // 2^8); what follows is linear, so each group forms its share and the two
   // are added last
   {
-    float yr = 0.0f, yi = 0.0f;
+    double yr = 0.0, yi = 0.0;
 #pragma unroll
     for (int st = 0; st < T; ++st) {
       float re[2][2], im[2][2];  // [matrix][component]
@@ -236,20 +238,20 @@ __global__ __launch_bounds__(64 * kWaves, T <= 2 ? 4 : 2) void dec_split_f4_kern
             re[mm][k] = vS - im[mm][k];
           }
         }
-      const float u_re = GS ? 1.0f : sc[0][st][0], u_im = GS ? 1.0f : sc[0][st][1];
-      const float w_re = GS ? 1.0f : sc[1][st][0], w_im = GS ? 1.0f : sc[1][st][1];
-      yr = fmaf(u_re, re[0][0], yr);
-      yr = fmaf(-u_im, im[0][1], yr);
-      yr = fmaf(w_re, re[1][0], yr);
-      yr = fmaf(w_im, im[1][1], yr);
-      yi = fmaf(u_re, re[0][1], yi);
-      yi = fmaf(u_im, im[0][0], yi);
-      yi = fmaf(-w_re, re[1][1], yi);
-      yi = fmaf(w_im, im[1][0], yi);
+      const double u_re = GS ? 1.0f : sc[0][st][0], u_im = GS ? 1.0f : sc[0][st][1];
+      const double w_re = GS ? 1.0f : sc[1][st][0], w_im = GS ? 1.0f : sc[1][st][1];
+      yr = fma(u_re, (double)re[0][0], yr);
+      yr = fma(-u_im, (double)im[0][1], yr);
+      yr = fma(w_re, (double)re[1][0], yr);
+      yr = fma(w_im, (double)im[1][1], yr);
+      yi = fma(u_re, (double)re[0][1], yi);
+      yi = fma(u_im, (double)im[0][0], yi);
+      yi = fma(-w_re, (double)re[1][1], yi);
+      yi = fma(w_im, (double)im[1][0], yi);
     }
-    yr = fmaf(__shfl_down(yr, 16), 1.0f / kBand2Scale, yr);
-    yi = fmaf(__shfl_down(yi, 16), 1.0f / kBand2Scale, yi);
-    if (!(g & 1)) part[kw][2 * tile + (g >> 1)][li] = make_float2(yr, yi);  // zero for a wave without steps
+    yr = fma(__shfl_down(yr, 16), 1.0 / kBand2Scale, yr);
+    yi = fma(__shfl_down(yi, 16), 1.0 / kBand2Scale, yi);
+    if (!(g & 1)) part[kw][2 * tile + (g >> 1)][li] = make_double2(yr, yi);  // zero for a wave without steps
   }
   __syncthreads();
   if (tid >= 16 * B) return;
@@ -258,8 +260,8 @@ __global__ __launch_bounds__(64 * kWaves, T <= 2 ? 4 : 2) void dec_split_f4_kern
   double yr = 0.0, yi = 0.0;
 #pragma unroll
   for (int w = 0; w < KW; ++w) {
-    yr += (double)part[w][b][r].x;
-    yi += (double)part[w][b][r].y;
+    yr += part[w][b][r].x;
+    yi += part[w][b][r].y;
   }
   float mb = 0.0f;
 #pragma unroll

@@ -280,3 +280,22 @@ def test_group_fp4_launch_lines(gpu, T, B, G, shapes):
     errs = [rel_l2(host(a[6]), r) for a, r in zip(args, refs)]
     print(f"T={T} B={B} G={G} {shapes}:", " ".join(f"{e:.2e}" for e in errs))
     assert max(errs) <= 1e-6  # two digit bands, float sums: as for the one launch and the streaming product above
+
+
+@pytest.mark.parametrize("T,B", [(1, 1), (1, 4), (2, 2), (3, 4), (4, 2)])
+def test_group_fp4_one_step_rounded_once(gpu, T, B):
+    """A layer of one 64-code step, per-tensor scales: the matrix core's sums of
+    so few digits are exact and are recombined in double, so the outputs' own
+    rounding is the error: within 2^-24 a value, 2^-24 / sqrt(3) in 2-norm."""
+    import torch
+    import paper_2512_02901_amd as f2
+    rng = np.random.default_rng((64, T, B))
+    N, K = 256, 64
+    cu, cw = (rng.integers(0, 256, (T, N, K // 4)).astype(np.uint8) for _ in range(2))
+    su, sw = (rng.uniform(0.01, 0.02, (T, 2)).astype(np.float32) for _ in range(2))
+    x = bf16_tokens(rng, B, K)
+    y = torch.empty((B, N), dtype=torch.complex64, device=gpu)
+    f2.WlGroup([(f2.repack_tiled_fp4(dev(cu, gpu)), dev(su, gpu), f2.repack_tiled_fp4(dev(cw, gpu)), dev(sw, gpu),
+                 bf16_dev(x, gpu), None, y)], T=T, B=B, layout=f2.LAYOUT_TILED_FP4).run()
+    want = x @ oracle.dequantize(oracle.unpack(cu, K), su).T + np.conj(x) @ oracle.dequantize(oracle.unpack(cw, K), sw).T
+    assert rel_l2(host(y), want) <= 2.0 ** -24 / np.sqrt(3)
