@@ -183,12 +183,14 @@ constexpr int kFlushRounds = 128;  // rounds of kQzUnroll bytes (1024 values) be
 // blocks of 256, four per CU (512 blocks of 512 measured a tenth slower).
 // kQzUnroll: with four bytes a round a thread took 132 registers or more, so
 // three blocks fit a CU and the grid ended in a second, nearly empty round;
-// with two it takes 100 and all 1024 are resident.  2048 x 2048, T = 2, U and
+// with two the stages take 100, 106, 120 and (capped, two of them in memory;
+// 130 without: a T = 4 call of 5504 x 2048 134 us, now 130) 128, and all 1024
+// are resident.  2048 x 2048, T = 2, U and
 // W with their conversion and repacking: 106.4 -> 96.1 us (four bytes capped
 // at 128 registers spill: 113; one byte and the next round's loads ahead:
 // 95.3, two bytes and those: 99.6).
 template <int T0>
-__global__ __launch_bounds__(kQzThreads) void qz_stage_kernel(const float2* __restrict__ M, int64_t nbytes,
+__global__ __launch_bounds__(kQzThreads, T0 == 3 ? 4 : 1) void qz_stage_kernel(const float2* __restrict__ M, int64_t nbytes,
                                                               uint8_t* __restrict__ codes,
                                                               float* __restrict__ scales,
                                                               unsigned long long* __restrict__ tot) {
@@ -218,8 +220,8 @@ __global__ __launch_bounds__(kQzThreads) void qz_stage_kernel(const float2* __re
       for (int tp = 0; tp < T0; ++tp) prev[u][tp] = ok ? codes[(int64_t)tp * nbytes + bi] : 0u;
     }
   };
-  // the first round is asked for before anything is waited for: a matrix of
-  // up to 4 M entries has no other
+  // the first round is asked for before anything is waited for: a matrix of up
+  // to kQzMaxBlocks * kQzThreads * kQzUnroll * 4 = 2 M entries has no other
   int64_t w0 = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x - lane);
   load_round(w0 + lane);
   for (int i = threadIdx.x; i < kPartWords; i += blockDim.x) acc[i] = 0ull;
