@@ -15,6 +15,8 @@ oracle's rounding only by one step at a near-tie (the oracle's unrounded
 value within TOL_TIE times the stage's RMS of the midpoint).  The end-to-end difference is
 printed and held to a loose sanity bound.
 """
+import math
+
 import numpy as np
 import pytest
 
@@ -300,8 +302,8 @@ def test_block_attention_runs(gpu, n, H, pos, hidden):
         w[name] = (cu, s, cw, s)
     gains = torch.ones(2 * n, device=gpu)
     blk = f2.WlBlock(w, gains, gains, n=n, n_ff=f, n_heads=H, T=T, max_ctx=pos + 3)
-    x, k, v = (torch.view_as_complex(torch.randn((*s, 2), generator=g, device=gpu))
-               for s in ((1, n), (H, pos + 3, dc), (H, pos + 3, dc)))
+    x, k, v = (torch.view_as_complex(torch.randn((math.prod(s) + 1, 2), generator=g, device=gpu))[1:].view(s)
+               for s in ((1, n), (H, pos + 3, dc), (H, pos + 3, dc)))  # 8-byte aligned only
     blk.decode(x, k, v, pos)
     q = blk.intermediates()["q_rot"].clone().view(H, dc)
     low = min(hidden, pos)
@@ -310,11 +312,12 @@ def test_block_attention_runs(gpu, n, H, pos, hidden):
     out = blk.decode(x, k, v, pos)
     got = as_complex(blk.intermediates()["o"])
     assert torch.equal(out, blk.decode(x, k, v, pos))
-    qd, kd = (torch.view_as_real(t).double().flatten(-2) for t in (q, k[:, :pos + 1]))
+    # on the CPU: the device's own float64 softmax is only 1e-7 accurate
+    qd, kd = (torch.view_as_real(t.cpu()).double().flatten(-2) for t in (q, k[:, :pos + 1]))
     scores = torch.matmul(kd, qd.unsqueeze(-1)).squeeze(-1) / (2 * dc) ** 0.5
     p = torch.softmax(scores, -1).unsqueeze(1)
-    vd = v[:, :pos + 1].to(torch.complex128)
-    want = torch.complex(torch.matmul(p, vd.real.contiguous()), torch.matmul(p, vd.imag.contiguous())).flatten().cpu().numpy()
+    vd = v[:, :pos + 1].cpu().to(torch.complex128)
+    want = torch.complex(torch.matmul(p, vd.real.contiguous()), torch.matmul(p, vd.imag.contiguous())).flatten().numpy()
     assert np.isfinite(got).all()
     for a, b in ((got.real, want.real), (got.imag, want.imag)):
         assert (np.abs(a - b) <= 2.0 ** -8 * (1 + 2.0 ** -15) * np.abs(b)).all()
