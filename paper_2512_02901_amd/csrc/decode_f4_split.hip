@@ -290,6 +290,8 @@ void launch_split_f4_t(const SplitGroup& a, bool gs, unsigned blocks, hipStream_
 
 }  // namespace
 
+constexpr int64_t kCUs = 256;
+
 // Every block encodes its tokens itself, over all of K, so the one launch costs
 // more per row block and 256-code step than the streaming product, against the
 // two launches it saves.  What it costs goes with the steps that the row blocks
@@ -318,7 +320,32 @@ void launch_split_f4_t(const SplitGroup& a, bool gs, unsigned blocks, hipStream_
 //          1024 (8 x 2048 x 2048) 14 / 19, 24 / 24; 1328 22.1 / 21.9, 43.4 / 30.7
 //   T = 3  384 4 tokens 16.7 / 19.8; 688 (n = 1536) 2 tokens 19.2 / 17.6
 //   T = 4  384 1 token 12.8 / 16.7; 688 (n = 1024) 2 tokens 17.7 / 16.7
-constexpr int64_t kCUs = 256;
+// Blocks beyond those resident (two a CU, one from T = 3 on) wait for a second
+// round, which costs a whole one however few they are; the streaming product
+// spreads any number evenly.  What that wastes goes with the steps that the CUs
+// idle in the last round (waste) and, where the waves on a row block are few, with
+// all steps of the rounds (full), steps per CU:
+//   T = 1  4 tokens  520 x 4096 columns (row blocks x columns), waste 31, 22.7 / 20.4; 640, 24, equal
+//   T = 2  2 tokens  520 x 5504, waste 43, 23.1 / 21.3; 520 x 4096, 31, equal
+//          4 tokens  520 x 4096, full 64, 29.1 / 21.3, G = 256 35.3 / 28.6; 2048, full 32, pays
+//   T = 3  1, 2      260 x 5504, waste 22, 19.0 / 18.2, 21.9 / 19.1; 260 x 4096, 16, pays;
+//                    G = 256 260 x 4096, 16, 20.2 / 18.6; 320 x 4096, 12, 20.9 / 20.3; 384 x 4096, 8, pays
+//          4 tokens  260 x 3072, full 24, 20.9 / 19.9; 4096, 32, 27.1 / 20.4; 2048, 16, pays;
+//                    G = 256 260 x 1984, waste 8, 18.7 / 17.0; 352, 5, 19.0 / 18.7; 384, 4, 19.1 / 20.1
+//   T = 4  1 token   260 x 5504, waste 22, 21.5 / 20.9; 2 tokens 260 x 4096, 16, 19.3 / 18.7, 384 x 8192, 16, 33.0 / 31.8;
+//                    G = 256 260 x 4096, 16 steps, 23.5 / 20.4, 384 x 4096, waste 8, 24.4 / 22.9; 260 x 3072 17.1 / 20.4
+bool last_round_wasted(int T, int B, bool gs, int64_t blocks, int longest) {
+  const int64_t resident = T >= 3 ? kCUs : 2 * kCUs, slots = (blocks + resident - 1) / resident * resident;
+  if (slots == resident) return false;
+  const int64_t waste = (slots - blocks) * longest / kCUs, full = slots * longest / kCUs;
+  switch (T) {
+    case 1: return B > 2 && waste >= 28;
+    case 2: return B > 2 ? full > 32 : B == 2 && !gs && waste >= 40;
+    case 3: return B > 2 ? full > 16 || (gs && waste >= 5) : waste >= (gs ? 12 : 15);
+    default: return gs ? longest >= 16 && waste >= 8 : waste >= (B == 1 ? 20 : 15);
+  }
+}
+
 
 bool f4_split_ok(const DecHeader& h, const DecLayer* tab) {
   if (h.mode != kModeBf16F4 || h.bands != 2 || h.n_layers > kSplitLayers) return false;
@@ -342,6 +369,7 @@ bool f4_split_ok(const DecHeader& h, const DecLayer* tab) {
   if (longest == 1 && blocks > 2 * kCUs && (h.T > 1 || h.B == 2)) return false;
   if (blocks > kCUs * (h.T >= 3 ? 2 : h.T == 2 && h.B > 2 ? 3 : 4)) return false;
   const bool gs = h.grouped != 0;
+  if (last_round_wasted(h.T, h.B, gs, blocks, longest)) return false;
   int64_t most;  // steps per CU
   switch (h.T) {
     case 1: most = h.B == 1 ? 128 : h.B <= 3 ? 64 : 48; break;

@@ -257,10 +257,15 @@ def test_group_fp4_one_launch_and_streaming(gpu, T, B, G):
 @pytest.mark.parametrize("T,B,G,shapes", [
     (2, 3, 0, [(40, 6144)]), (2, 3, 0, [(40, 6208)]), (1, 4, 256, [(1040, 6208)]), (1, 4, 256, [(1008, 6208)]),
     (2, 2, 0, [(8192, 64)]), (2, 2, 0, [(8208, 64)]), (3, 4, 0, [(2048, 768), (2048, 768)]),
-    (3, 4, 0, [(4096, 3136)]), (4, 2, 256, [(4112, 3136)])])
+    (3, 4, 0, [(4096, 3136)]), (4, 2, 256, [(4112, 3136)]),
+    # a second round of blocks, short and long rows
+    (1, 4, 0, [(8208, 2048)]), (1, 4, 0, [(8208, 4096)]), (2, 4, 0, [(8208, 2048)]), (2, 3, 0, [(8208, 2112)]),
+    (2, 2, 0, [(8208, 5504)]), (3, 2, 0, [(4112, 4096)]), (3, 4, 256, [(4112, 1984)]), (3, 3, 0, [(4112, 2112)]),
+    (4, 1, 0, [(4112, 5504)]), (4, 1, 256, [(4112, 4096)])])
 def test_group_fp4_launch_lines(gpu, T, B, G, shapes):
     """Either side of the lines between the one launch and the streaming
-    product: steps of a layer, row blocks of one step, steps per CU."""
+    product: steps of a layer, row blocks of one step, steps per CU, steps that
+    CUs idle in a last round."""
     import torch
     import paper_2512_02901_amd as f2
     from oracle import groups as og
