@@ -77,6 +77,10 @@ size_t single_decode_bytes(int64_t N, int64_t K, int32_t T, int64_t B, int32_t d
 bool one_launch_pays(const WlArgs& a) {
   const int64_t rb = (a.N + 15) / 16, steps = (a.K + 255) / 256, B = a.B, K = a.K;
   const int32_t T = a.T;
+  // From T = 3 on one block of eight waves fills a CU (256 of them): a few row
+  // blocks more leave most CUs idle for `waste` steps of a second round, while
+  // the other side spreads any number evenly.
+  const int64_t waste = rb > 256 && rb < 512 ? (512 - rb) * steps / 256 : 0;
   if (B > FAIRY2I_MAX_DECODE_BATCH) {
     // Against the prefill GEMM, whose time hardly grows while its own blocks
     // (32 x 64) do not fill the GPU, but which walks K in one block: the
@@ -108,6 +112,12 @@ bool one_launch_pays(const WlArgs& a) {
     // (2752) 135 / 149, 24000 x 4096 4 (3000) 118 / 115, 6 (4500) 169 / 196 (the
     // other side's cost for 5, 6 and 9 .. 12 tokens is that of 8 and 16); one token of 128256 x
     // 2048 T = 2 113 / 101.
+    // T = 3, 260 row blocks (4160 rows) x 4096, one token, waste 15, 19.8 / 19.2, 344 x
+    // 8192, 21, 34.9 / 31.9, 384 x 4096, 8, 21.8 / 21.6, two tokens 280 x 8192, 29, 36.1 /
+    // 34.4; T = 4 260 x 4096, one token, 24.9 / 22.2, 344 x 4096, 10, 26.3 / 23.9, 384 x
+    // 4096, 8, equal, two tokens 260 x 8192, 31, 42.0 / 39.8, 320 x 8192, 24, 43.0 / 43.5.
+    if (T == 3 && B <= 2 && waste >= (B == 1 ? 14 : 27)) return false;
+    if (T == 4 && B <= 2 && waste >= (B == 1 ? 10 : 27) && steps >= 16) return false;
     const int64_t most = T == 1 ? 9000 : T == 2 ? (B > 8 && B <= 12 ? 9000 : 4500)
                          : T == 3 ? 6000 : (B > 4 && B <= 6 ? 4500 : 2800);
     return rb <= (T == 1 || (T == 2 && B > 2) ? 1536 : 2048) && rb * ((B + 1) / 2) <= most;
@@ -129,6 +139,9 @@ bool one_launch_pays(const WlArgs& a) {
   if (T == 3 && steps >= 64) return steps <= 512 && (B > 8 || (B > 4 && rb <= 16));
   if (T == 2 && steps > 64) return steps <= 512 && (B > 4 || rb <= 16);
   if (T == 1 && steps > 64) return B > 4 || rb <= 16 || (B > 2 && steps <= 128);
+  // T = 3, 260 row blocks x 5504, one token, waste 21, 21.6 / 19.8, 384 x 8192, 16, 28.0 /
+  // 27.0, 280 x 5504, 19, equal; four tokens 260 x 8192, 31, 27.2 / 26.1, 320 x 8192, 24, equal.
+  if (T == 3 && B <= 4 && waste >= (B > 2 ? 26 : steps >= 28 ? 16 : 21)) return false;
   // Many rows: 24000 x 4096 T = 1 1 token 22.9 / 21.1, 24000 x 2048 8 15.6 / 19.5,
   // 32000 x 4096 16 32 / 56; T = 2 32000 x 4096 1 42.5 / 42, 128256 x 2048 8
   // 99 / 89; T = 3 24000 x 2048 1 27.1 / 25.2, 8 28 / 32, 24000 x 4096 1 45 / 46;

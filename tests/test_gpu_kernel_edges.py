@@ -205,7 +205,10 @@ def test_bf16_layer_edges(gpu, N, K, B, T):
     ("i8", 1, 16384, 64, 3), ("i8", 1, 16400, 64, 3), ("i8", 4, 33, 5504, 4), ("i8", 4, 33, 5696, 4),
     ("i8", 4, 4112, 64, 2), ("i8", 4, 32, 8256, 16), ("i8", 3, 17, 16128, 1), ("i8", 3, 17, 16384, 1),
     ("i8", 2, 272, 16640, 4), ("i8", 2, 16, 16640, 4), ("i8", 3, 16384, 64, 32), ("i8", 2, 8192, 64, 17),
-    ("i8", 4, 4096, 256, 33), ("i8", 2, 7680, 320, 48), ("i8", 3, 7680, 320, 48)])
+    ("i8", 4, 4096, 256, 33), ("i8", 2, 7680, 320, 48), ("i8", 3, 7680, 320, 48),
+    # one block a CU and a few more, short and long rows
+    ("bf16", 3, 4112, 2048, 1), ("bf16", 3, 4112, 4096, 1), ("bf16", 4, 4112, 8192, 2), ("i8", 3, 4112, 5504, 2),
+    ("i8", 3, 4112, 8192, 4)])
 def test_layer_launch_lines(gpu, dt, T, N, K, B):
     import torch
     import paper_2512_02901_amd as f2
